@@ -63,6 +63,8 @@ constexpr int SC_STOP = 10, SC_COUNT = 11, SC_RR0 = 12;
 // Flexible CG (FP64, device scalars): p.q, r.r of the new residual, breakdown flag,
 // alpha, z.r_new and z.r_old of the Polak-Ribiere beta, r.z alternating (FCG_RZ + 0, 1).
 constexpr int FCG_PQ = 13, FCG_RR = 14, FCG_BRK = 15, FCG_ALPHA = 16, FCG_ZRN = 17, FCG_ZR = 18, FCG_RZ = 19;
+// Set when a workgroup of the one-launch coarse solve gave up waiting for the others.
+constexpr int SC_LOST = 21;
 constexpr int PCG_RECORD = 64;
 constexpr int SC_ALPHA = 32, SC_BETA = SC_ALPHA + PCG_RECORD, SC_N = SC_BETA + PCG_RECORD;
 
@@ -149,6 +151,34 @@ int ell_pcg_blocks(int64_t nn, bool node_major);
 hipError_t launch_ell_pcg_apply(int prec, bool node_major, int64_t nn, int W, const int32_t *cols,
                                 const void *vals, const void *z, const void *p_old, void *p_new, void *y, double *sc,
                                 const double *partial, int it, double rtol2, double *pq_part, hipStream_t s);
+// The whole Jacobi-PCG of the same operator in one launch (k_coarse_pcg): `groups`
+// workgroups own `rows` consecutive scalar rows each (a multiple of 256, at most
+// coarse_pcg_max_rows) and hold them in registers.  cols: uint16 [W][3 nn], where the
+// direction of the column's node starts in the row's workgroup: entry 3 n - row0 for a
+// node all of whose rows the workgroup owns, else rows + 3 k for node halo_ids[k] of its
+// list halo_ids[halo_off[g] .. halo_off[g + 1]).  slots: coarse_pcg_slots(nn) doubles.
+// Stops as dir2 does, or after maxit iterations; sets sc[SC_COUNT], and sc[SC_LOST] if a
+// workgroup waited longer than a bounded time for another (x is then not to be used).
+struct CoarsePcg {
+  int64_t nn;
+  int rows, groups, W, max_halo, maxit;
+  bool node_major;
+  double rtol2;
+  const void *vals;
+  const uint16_t *cols;
+  const int32_t *halo_off, *halo_ids;
+  const void *b, *dinv;
+  void *x;
+  void *z[2];  // exchange buffers, 3 nn values each
+  double *slots, *sc;
+};
+constexpr int COARSE_PCG_W = 27;  // most columns of a row
+// Every workgroup posts its sums in this many places, so that few read the same lines.
+constexpr int COARSE_PCG_COPIES = 8;
+int coarse_pcg_max_rows(int prec);
+size_t coarse_pcg_slots(int64_t nn);
+size_t coarse_pcg_lds(int prec, int rows, int max_halo);
+hipError_t launch_coarse_pcg(int prec, const CoarsePcg &a, hipStream_t s);
 // Assembles the order-1 element matrices of `op` (built in precision prec) into the
 // sliced-ELL blocks; constrained rows become identity rows, constrained columns zero.
 hipError_t launch_ell_build(const hpmg_op_s &op, int prec, bool node_major, int64_t W, const int32_t *cols,

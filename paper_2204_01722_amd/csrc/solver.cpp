@@ -3,9 +3,12 @@
 // in the library's kernels; the host reads back the few scalars that decide control
 // flow (CG coefficients, norms) through a pinned buffer.
 #include <algorithm>
+#include <condition_variable>
 #include <cstdint>
 #include <cmath>
 #include <cstdio>
+#include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -58,6 +61,15 @@ struct hpmg_mg_s {
   bool ell_ready = false;
   bool ell_node_major = false;  // block layout and PCG body (coarse_block_layout)
   uint64_t ell_version = 0;  // fine state version the blocks were built from
+  // The same level split over workgroups for the one-launch PCG (cp_groups = 0: not split):
+  // cp_rows rows each, the halo nodes of every workgroup and each column's place in it.
+  int cp_groups = 0, cp_rows = 0, cp_max_halo = 0;
+  bool cp_lost = false;  // its workgroups once waited in vain: not tried again on this handle
+  std::vector<int32_t> cp_off_host, cp_ids_host;
+  std::vector<uint16_t> cp_cols_host;
+  int32_t *cp_off = nullptr, *cp_ids = nullptr;
+  uint16_t *cp_cols = nullptr;
+  double *cp_slots = nullptr;
   // counters since creation: V-cycles, coarse iterations, operator applies per level
   int64_t n_vcycles = 0, n_coarse_its = 0, n_setups = 0;
   int64_t n_applies[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -89,6 +101,12 @@ size_t mg_layout(hpmg_mg_s *mg, char *base) {
     mg->ell_cols = reinterpret_cast<int32_t *>(take((size_t)mg->ell_w * nn * sizeof(int32_t)));
     mg->ell_vals = take((size_t)mg->ell_w * 9 * nn * es);
     C.p2 = take((size_t)C.n * es);
+  }
+  if (mg->cp_groups > 0) {
+    mg->cp_off = reinterpret_cast<int32_t *>(take(mg->cp_off_host.size() * sizeof(int32_t)));
+    mg->cp_ids = reinterpret_cast<int32_t *>(take(mg->cp_ids_host.size() * sizeof(int32_t)));
+    mg->cp_cols = reinterpret_cast<uint16_t *>(take(mg->cp_cols_host.size() * sizeof(uint16_t)));
+    mg->cp_slots = reinterpret_cast<double *>(take(coarse_pcg_slots(mg->lv.back().n / 3) * sizeof(double)));
   }
   for (Level &L : mg->lv) {
     const size_t nb = (size_t)L.n * es;
@@ -165,6 +183,98 @@ double tridiag_max_eig(const std::vector<double> &a, const std::vector<double> &
   return hi;
 }
 
+// The coarsest level's assembled blocks are those of the current linearisation.
+bool blocks_current(const hpmg_mg_s *mg) {
+  const hpmg_op_s *o = mg->lv.back().op, *src = o->fine ? o->fine : o;
+  return mg->ell_ready && mg->ell_version == src->state_version;
+}
+
+// Workgroups of the one-launch coarse solve wait for each other, so all of a launch must
+// be resident together.  At most one per compute unit and device is let in at a time:
+// a launch that would exceed that waits here until earlier ones have ended (another
+// thread's; they are read back before they leave).
+class ResidentGroups {
+ public:
+  ResidentGroups(int device, int groups, int limit) : device_(device), groups_(groups) {
+    std::unique_lock<std::mutex> lock(mutex());
+    freed().wait(lock, [&] { return in_use()[device_] + groups_ <= limit; });
+    in_use()[device_] += groups_;
+  }
+  ~ResidentGroups() {
+    {
+      std::lock_guard<std::mutex> lock(mutex());
+      in_use()[device_] -= groups_;
+    }
+    freed().notify_all();
+  }
+  ResidentGroups(const ResidentGroups &) = delete;
+  ResidentGroups &operator=(const ResidentGroups &) = delete;
+
+ private:
+  static std::mutex &mutex() {
+    static std::mutex m;
+    return m;
+  }
+  static std::condition_variable &freed() {
+    static std::condition_variable c;
+    return c;
+  }
+  static std::map<int, int> &in_use() {
+    static std::map<int, int> m;
+    return m;
+  }
+  int device_, groups_;
+};
+
+int compute_units(int *device, int *units) {
+  HPMG_HIP(hipGetDevice(device));
+  HPMG_HIP(hipDeviceGetAttribute(units, hipDeviceAttributeMultiprocessorCount, *device));
+  return HPMG_OK;
+}
+
+// The coarse solve of pcg_device (fixed = 0, nothing recorded) in one launch.  *done stays
+// false, and the caller solves again the other way, if the workgroups did not find each
+// other in time (another process held compute units).
+int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hipStream_t s, int *its_out,
+                   bool *done) {
+  int st, dev = 0, cus = 0;
+  *done = false;
+  if ((st = compute_units(&dev, &cus))) return st;
+  if (mg->cp_groups > cus) return HPMG_OK;
+  CoarsePcg a{};
+  a.nn = L.n / 3;
+  a.rows = mg->cp_rows;
+  a.groups = mg->cp_groups;
+  a.W = mg->ell_w;
+  a.max_halo = mg->cp_max_halo;
+  a.maxit = maxit;
+  a.node_major = mg->ell_node_major;
+  a.rtol2 = rtol * rtol;
+  a.vals = mg->ell_vals;
+  a.cols = mg->cp_cols;
+  a.halo_off = mg->cp_off;
+  a.halo_ids = mg->cp_ids;
+  a.b = L.b;
+  a.dinv = L.dinv;
+  a.x = L.x;
+  a.z[0] = L.z;
+  a.z[1] = L.t;
+  a.slots = mg->cp_slots;
+  a.sc = mg->scal;
+  ResidentGroups resident(dev, a.groups, cus);
+  HPMG_HIP(launch_coarse_pcg(prec, a, s));
+  if ((st = read_scalars(mg, SC_LOST + 1, s))) return st;
+  if (mg->host[SC_LOST] != 0.0) {
+    mg->cp_lost = true;
+    return HPMG_OK;
+  }
+  *its_out = (int)mg->host[SC_COUNT];
+  const size_t l = &L - mg->lv.data();
+  if (l < 8) mg->n_applies[l] += *its_out;
+  *done = true;
+  return HPMG_OK;
+}
+
 // Jacobi-PCG on level L from x = 0 with right-hand side L.b: fixed > 0 runs exactly that
 // many iterations (fewer on a breakdown, p.Ap <= 0), otherwise it stops at
 // ||r|| <= rtol ||b|| or after maxit iterations.  Every scalar stays on the device and
@@ -190,8 +300,7 @@ int pcg_device(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, int fi
   const double rtol2 = fixed > 0 ? -1.0 : rtol * rtol;
   // The assembled coarsest level (when its blocks match the current linearisation)
   // takes two launches per iteration; otherwise four.
-  const hpmg_op_s *src = L.op->fine ? L.op->fine : L.op;  // holder of the level's linearisation
-  const bool ell = !record && l + 1 == mg->lv.size() && mg->ell_ready && mg->ell_version == src->state_version;
+  const bool ell = !record && l + 1 == mg->lv.size() && blocks_current(mg);
   const int64_t nn = L.n / 3;
   const int nb_pq = ell ? ell_pcg_blocks(nn, mg->ell_node_major) : (int)((nn + 255) / 256);
   int queued = 0, its = limit;
@@ -269,8 +378,13 @@ int cycle(hpmg_mg_s *mg, int l, hipStream_t s) {
   Level &L = mg->lv[l];
   if (l + 1 == (int)mg->lv.size()) {
     int its = 0;
-    st = pcg_device(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, mg->prm.coarse_fixed_its,
-                    mg->last_coarse_its, 4, s, &its);
+    bool done = false;
+    if (mg->cp_groups > 0 && !mg->cp_lost && mg->prm.coarse_fixed_its <= 0 && blocks_current(mg) &&
+        (st = pcg_one_launch(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, s, &its, &done)))
+      return st;
+    if (!done)
+      st = pcg_device(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, mg->prm.coarse_fixed_its,
+                      mg->last_coarse_its, 4, s, &its);
     mg->last_coarse_its = its;
     mg->n_coarse_its += its;
     return st;
@@ -337,6 +451,56 @@ int build_ell_structure(hpmg_mg_s *mg) {
     for (int k = 0; k < w; ++k)
       mg->ell_cols_host[(size_t)k * nn + n] = k < cnt[n] ? nb[(size_t)n * ELL_MAX_W + k] : (int32_t)(-1 - n);
   mg->ell_w = w;
+  return HPMG_OK;
+}
+
+// Splits the assembled coarsest level over the workgroups of the one-launch PCG; leaves
+// cp_groups = 0 where it does not fit (more rows than the device's compute units hold in
+// registers, rows wider than a hexahedral mesh's, or halos that do not fit in LDS).
+int build_coarse_split(hpmg_mg_s *mg) {
+  const int64_t nn = mg->lv.back().n / 3, n3 = 3 * nn;
+  const int W = mg->ell_w, prec = prec_of(mg);
+  int dev = 0, cus = 0, st;
+  if ((st = compute_units(&dev, &cus))) return st;
+  int rows = 512;
+  while (rows < coarse_pcg_max_rows(prec) && (n3 + rows - 1) / rows > cus) rows *= 2;
+  const int64_t G = (n3 + rows - 1) / rows;
+  if (W > COARSE_PCG_W || G > cus) return HPMG_OK;
+  std::vector<int32_t> off(1, 0), ids, place(nn, -1), in(nn, -1);
+  std::vector<uint16_t> cols((size_t)W * n3);
+  int max_halo = 0;
+  for (int64_t g = 0; g < G; ++g) {
+    const int64_t row0 = g * rows, row1 = std::min(n3, row0 + rows);
+    int nh = 0;
+    for (int64_t n = row0 / 3; 3 * n < row1; ++n)
+      for (int j = 0; j < W; ++j) {
+        int64_t c = mg->ell_cols_host[(size_t)j * nn + n], at;
+        if (c < 0) c = -1 - c;  // padding: the node itself, with a zero block
+        if (3 * c >= row0 && 3 * c + 3 <= row1) {
+          at = 3 * c - row0;
+        } else {
+          if (in[c] != (int32_t)g) {
+            in[c] = (int32_t)g;
+            place[c] = nh++;
+            ids.push_back((int32_t)c);
+          }
+          at = rows + 3 * (int64_t)place[c];
+        }
+        if (at > 65535) return HPMG_OK;  // 16 bits in the kernel
+        for (int64_t d = std::max(3 * n, row0); d < std::min(3 * n + 3, row1); ++d)
+          cols[(size_t)j * n3 + d] = (uint16_t)at;
+      }
+    off.push_back((int32_t)ids.size());
+    max_halo = std::max(max_halo, nh);
+  }
+  if (coarse_pcg_lds(prec, rows, max_halo) > (size_t)60 * 1024) return HPMG_OK;
+  if (ids.empty()) ids.push_back(0);  // one workgroup: nothing to fetch
+  mg->cp_groups = (int)G;
+  mg->cp_rows = rows;
+  mg->cp_max_halo = max_halo;
+  mg->cp_off_host.swap(off);
+  mg->cp_ids_host.swap(ids);
+  mg->cp_cols_host.swap(cols);
   return HPMG_OK;
 }
 
@@ -565,7 +729,8 @@ int hpmg_mg_create(const hpmg_op *levels, int n_levels, const hpmg_mg_params *pa
   if (!redisc && params->coarse_element_matrices && mg->lv.back().op->P == 2) {
     const int64_t nn = mg->lv.back().n / 3;
     mg->ell_node_major = params->coarse_block_layout < 0 ? nn >= ELL_NODE_MAJOR_MIN : params->coarse_block_layout == 1;
-    const int st = build_ell_structure(mg);
+    int st = build_ell_structure(mg);
+    if (!st && mg->ell_w > 0) st = build_coarse_split(mg);
     if (st) {
       delete mg;
       return st;
@@ -603,6 +768,14 @@ int hpmg_mg_bind_workspace(hpmg_mg mg, void *ws, size_t bytes) {
   if (mg->ell_w > 0)
     HPMG_HIP(hipMemcpy(mg->ell_cols, mg->ell_cols_host.data(), mg->ell_cols_host.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice));
+  if (mg->cp_groups > 0) {
+    HPMG_HIP(hipMemcpy(mg->cp_off, mg->cp_off_host.data(), mg->cp_off_host.size() * sizeof(int32_t),
+                       hipMemcpyHostToDevice));
+    HPMG_HIP(hipMemcpy(mg->cp_ids, mg->cp_ids_host.data(), mg->cp_ids_host.size() * sizeof(int32_t),
+                       hipMemcpyHostToDevice));
+    HPMG_HIP(hipMemcpy(mg->cp_cols, mg->cp_cols_host.data(), mg->cp_cols_host.size() * sizeof(uint16_t),
+                       hipMemcpyHostToDevice));
+  }
   // Injection maps of rediscretised levels: coarse local node (a1, a2, a3) of an
   // element sits at fine local node (s a1, s a2, s a3), s = (Pf - 1) / (Pc - 1).
   for (size_t l = 1; l < mg->lv.size(); ++l) {

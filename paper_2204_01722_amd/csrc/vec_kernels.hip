@@ -6,6 +6,8 @@
 // cross-lane shuffles, the four wavefronts of a workgroup combine through LDS, and a
 // single workgroup sums the RED_BLOCKS partials in a fixed tree.  The result does not
 // depend on timing, so repeated runs are bitwise identical.
+#include <algorithm>
+
 #include "common.h"
 
 namespace hpmg {
@@ -492,7 +494,418 @@ __global__ __launch_bounds__(BS) void k_ell_pcg_nodes(int64_t nn, int W, const i
   block_store<1>(v, pq_part);
 }
 
+// ---- the whole coarse solve in one launch -------------------------------------------
+// Launched iteration by iteration, the assembled coarse level is bound by latency while its
+// blocks stay on the chip: two launches, two passes over the partial sums and nine dependent
+// rounds of loads, 21-24 us an iteration from 5^3 to 26^3 nodes, of which the blocks
+// themselves (18 MB at 21^3 in FP64) would take 3.  The register files of the 256 compute
+// units hold 128 MB, so here a thread keeps a scalar row (81 entries) for the whole solve;
+// what remains of an iteration is two sums over the grid, each a store and a load through
+// the memory side (about 1.5 us), the neighbours' z fetched while the first is under way,
+// and 81 LDS reads a row.  Measured per iteration, launch to launch: 11^3 nodes 24 -> 4.4 us
+// (FP64), 21^3 23.6 -> 5.8 us (FP64), 26^3 25 -> 6.8 us (FP32); a whole V-cycle on 20^3 Q4
+// elements 1587 -> 917 us in FP64 and 1278 -> 680 us in FP32.
+// 512 rows a workgroup and not fewer, since the sums cost more with every workgroup that
+// posts and reads them (21^3 nodes: 55 workgroups 191 us a solve, 127 221, 251 275); the
+// same sums in the same order as the launches' kernels, so the results are the same bits.
+constexpr int CP_NT = 512;
+constexpr int CP_RING = 8;  // sets of slots in rotation
+// What a slot or an exchanged value holds while it is empty: a NaN that no arithmetic
+// produces (a NaN to be posted is replaced by the plain one).
+template <typename T>
+struct CpBits;
+template <>
+struct CpBits<double> {
+  using U = unsigned long long;
+  static constexpr U EMPTY = 0x7ff8c0a45e5e7c01ull;
+  static __device__ __forceinline__ U of(double v) {
+    return (U)__double_as_longlong(v == v ? v : __builtin_nan(""));
+  }
+  static __device__ __forceinline__ double value(U u) { return __longlong_as_double((long long)u); }
+};
+template <>
+struct CpBits<float> {
+  using U = unsigned int;
+  static constexpr U EMPTY = 0x7fc5e7c1u;
+  static __device__ __forceinline__ U of(float v) { return __float_as_uint(v == v ? v : __builtin_nanf("")); }
+  static __device__ __forceinline__ float value(U u) { return __uint_as_float(u); }
+};
+constexpr long long CP_WAIT_TICKS = 10000000;  // 100 ms of the 100 MHz clock
+
+template <typename U>
+__device__ __forceinline__ U agent_load(const U *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename U>
+__device__ __forceinline__ void agent_store(U *p, U v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Empties the slots and both exchange buffers.
+template <typename T>
+__global__ void k_coarse_begin(CoarsePcg a, int64_t n_slots) {
+  using B = CpBits<T>;
+  typename B::U *z0 = (typename B::U *)a.z[0], *z1 = (typename B::U *)a.z[1];
+  unsigned long long *slots = reinterpret_cast<unsigned long long *>(a.slots);
+  GRID_STRIDE(i, n_slots) { slots[i] = CpBits<double>::EMPTY; }
+  GRID_STRIDE(i, 3 * a.nn) {
+    z0[i] = B::EMPTY;
+    z1[i] = B::EMPTY;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[SC_COUNT] = a.sc[SC_LOST] = 0.0;
+}
+
+// Sum over the wave in the order of wave_sum (lanes 32 apart, then 16, 8, 4, 2 and 1), in
+// every lane, by lane moves of the vector ALU instead of an LDS round trip a step.
+__device__ __forceinline__ double lane_pair(double v, int lo, int hi) {
+  return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double add_rotated(double v) {
+  const long long b = __double_as_longlong(v);
+  return lane_pair(v, __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false),
+                   __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double wave_total(double v) {
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((int)b, (int)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((int)(b >> 32), (int)(b >> 32), false, false);
+    v = lane_pair(__longlong_as_double(((long long)(int)hi[0] << 32) | (unsigned)lo[0]), (int)lo[1], (int)hi[1]);
+  }
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((int)b, (int)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((int)(b >> 32), (int)(b >> 32), false, false);
+    v = lane_pair(__longlong_as_double(((long long)(int)hi[0] << 32) | (unsigned)lo[0]), (int)lo[1], (int)hi[1]);
+  }
+  v = add_rotated<0x128>(v);  // row_ror:8, 4, 2, 1
+  v = add_rotated<0x124>(v);
+  v = add_rotated<0x122>(v);
+  return add_rotated<0x121>(v);
+}
+
+template <int RPT>
+struct CpShared {
+  double part[2][RPT][CP_NT / 64], total[2][4];
+  int lost;
+};
+
+// Sums NV values over all rows, in the same order in every workgroup and in the order of
+// the launch-per-iteration form: a partial for every BS rows (four waves each), then these
+// as block_reduce_fixed_n does, or as k_final does for the FIRST sums.  Each workgroup
+// posts its partials in set `epoch` % 8 of the slots, and its first waves read everybody's
+// while the others run `meanwhile(first thread, threads)`.  A slot is emptied four epochs
+// before it is used again: all have read it then (when a workgroup posts epoch e, all have
+// read epoch e - 2), and an ACK call (every other one) lies in between, which posts only
+// after all that its workgroup stored before has been acknowledged.
+// false: a wait took over 100 ms (every thread of the workgroup agrees).
+template <int NV, int RPT, bool ACK, bool FIRST, typename F>
+__device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const double (&in)[RPT][NV], double (&out)[NV],
+                                       CpShared<RPT> &sh, F meanwhile) {
+  using B = CpBits<double>;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, G = a.groups, K = a.rows / BS;
+  const int nb = (int)((3 * a.nn + BS - 1) / BS);
+#pragma unroll
+  for (int s = 0; s < RPT; ++s)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const double w = wave_total(in[s][k]);
+      if (lane == 0) sh.part[k][s][wid] = w;
+    }
+  if (ACK) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  const int pollers = FIRST ? 1 : nb < 256 ? (nb + 63) / 64 : 4;
+  if (wid < pollers) {
+    // partial k of this workgroup's block b: rows BS b .. BS (b + 1)
+    auto partial = [&](int k, int b) {
+      const double *w = &sh.part[k][b / (CP_NT / BS)][b % (CP_NT / BS) * (BS / 64)];
+      double t = 0.0;
+#pragma unroll
+      for (int j = 0; j < BS / 64; ++j) t += w[j];
+      return t;
+    };
+    unsigned long long *slots = reinterpret_cast<unsigned long long *>(a.slots);
+    const size_t copy = (size_t)CP_RING * 2 * nb, set = (size_t)(epoch % CP_RING) * 2 * nb;
+    if (G > 1 && wid == 0) {
+      const int b = lane / COARSE_PCG_COPIES, gb = blockIdx.x * K + b;
+      if (b < K && gb < nb) {
+        unsigned long long *mine = slots + lane % COARSE_PCG_COPIES * copy + gb;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) agent_store(mine + set + k * nb, B::of(partial(k, b)));
+        const size_t later = (size_t)((epoch + CP_RING / 2) % CP_RING) * 2 * nb;
+        agent_store(mine + later, B::EMPTY);
+        agent_store(mine + later + nb, B::EMPTY);
+      }
+    }
+    const unsigned long long *read = slots + (blockIdx.x % COARSE_PCG_COPIES) * copy + set;
+    const long long t0 = wall_clock64();
+    // the sums of block i < nb
+    auto get = [&](int i, double (&x)[NV]) {
+      if (G == 1) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) x[k] = partial(k, i);
+        return;
+      }
+      for (;;) {
+        unsigned long long q[NV];
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) q[k] = agent_load(read + k * nb + i);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+          all = all && q[k] != B::EMPTY;
+          x[k] = B::value(q[k]);
+        }
+        if (all) return;
+        if (wall_clock64() - t0 > CP_WAIT_TICKS) {
+          sh.lost = 1;
+          return;
+        }
+      }
+    };
+    double x[NV];
+    if constexpr (FIRST) {
+      double y[4][NV];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) y[q][k] = 0.0;
+        for (int i = lane + 64 * q; i < nb; i += BS) {
+          get(i, x);
+#pragma unroll
+          for (int k = 0; k < NV; ++k) y[q][k] += x[k];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const double t = wave_total((y[0][k] + y[2][k]) + (y[1][k] + y[3][k]));
+        if (lane < 4) sh.total[k][lane] = lane == 0 ? t : 0.0;
+      }
+    } else {
+      double y[NV];
+#pragma unroll
+      for (int k = 0; k < NV; ++k) y[k] = 0.0;
+      for (int i = tid; i < nb; i += BS) {
+        get(i, x);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) y[k] += x[k];
+      }
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const double t = wave_total(y[k]);
+        if (lane == 0) sh.total[k][wid] = t;
+      }
+      if (wid == 0 && lane >= pollers && lane < 4)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) sh.total[k][lane] = 0.0;
+    }
+  } else {
+    meanwhile(64 * pollers, CP_NT - 64 * pollers);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    out[k] = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) out[k] += sh.total[k][w];
+  }
+  return sh.lost == 0;
+}
+
+// The halo's z out of its exchange buffer into zh, by `count` threads from `first` on (a
+// value that is still empty has not arrived).
+template <typename T>
+__device__ __forceinline__ void cp_fetch(const typename CpBits<T>::U *__restrict__ zx, const int32_t *ids, T *zh,
+                                         int nh, int *lost, int first, int count) {
+  using B = CpBits<T>;
+  constexpr int NF = sizeof(T) == 4 ? 2 : 1;  // nodes whose loads are in flight together
+  const long long t0 = wall_clock64();
+  for (int u = (int)threadIdx.x - first; u < nh; u += NF * count) {
+    typename B::U q[NF][3];
+    int64_t from[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int uf = u + f * count;
+      from[f] = (int64_t)ids[uf < nh ? uf : u] * 3;
+    }
+    for (;;) {
+      bool all = true;
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q[f][k] = agent_load(zx + from[f] + k);
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) all = all && q[f][k] != B::EMPTY;
+      if (all) break;
+      if (wall_clock64() - t0 > CP_WAIT_TICKS) {
+        *lost = 1;
+        break;
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int uf = u + f * count;
+      if (uf < nh)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) zh[3 * uf + k] = B::value(q[f][k]);
+    }
+  }
+}
+
+template <typename T, int RPT>
+__global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
+  using B = CpBits<T>;
+  using U = typename B::U;
+  constexpr int W = COARSE_PCG_W;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ CpShared<RPT> sh;
+  const int tid = threadIdx.x, g = blockIdx.x;
+  const int64_t n3 = 3 * a.nn, row0 = (int64_t)g * a.rows;
+  const int rows = (int)(n3 - row0 < a.rows ? n3 - row0 : a.rows);
+  const int h0 = a.halo_off[g], nh = a.halo_off[g + 1] - h0;
+  T *p = reinterpret_cast<T *>(smem);                // directions: own rows, then the halo nodes'
+  T *ph = p + a.rows, *zh = ph + 3 * a.max_halo;     // the halo's part, and its z
+  int32_t *ids = reinterpret_cast<int32_t *>(zh + 3 * a.max_halo);
+  if (tid == 0) sh.lost = 0;
+  for (int u = tid; u < nh; u += CP_NT) ids[u] = a.halo_ids[h0 + u];
+  T A[RPT][3 * W], x[RPT], r[RPT], z[RPT], di[RPT], po[RPT];
+  uint32_t off[RPT][(W + 1) / 2];  // first entry of each column's direction, two to a word
+  bool whole[RPT];                 // the row's node is all in this workgroup
+  double v[RPT][2];
+  U *const z0 = (U *)a.z[0], *const z1 = (U *)a.z[1];
+#pragma unroll
+  for (int s = 0; s < RPT; ++s) {
+    const int row = tid + s * CP_NT;
+    const bool live = row < rows;
+    const int64_t d = row0 + (live ? row : 0), n = d / 3;
+    const int i = (int)(d - 3 * n);
+    whole[s] = live && 3 * n >= row0 && 3 * n + 3 <= row0 + rows;
+    const T *vals = (const T *)a.vals;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const bool in = live && j < a.W;
+      const uint32_t o = in ? a.cols[(int64_t)j * n3 + d] : 0u;
+      off[s][j / 2] = j % 2 ? off[s][j / 2] | (o << 16) : o;
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        A[s][3 * j + k] = !in            ? T(0)
+                          : a.node_major ? vals[((int64_t)j * 9 + 3 * i + k) * a.nn + n]
+                                         : vals[((int64_t)j * a.nn + n) * 9 + 3 * i + k];
+      if (j % 3 == 2) asm volatile("" ::: "memory");
+    }
+    x[s] = po[s] = T(0);
+    r[s] = live ? ((const T *)a.b)[d] : T(0);
+    di[s] = live ? ((const T *)a.dinv)[d] : T(0);
+    z[s] = di[s] * r[s];
+    if (live) agent_store(z0 + d, B::of(z[s]));
+    v[s][0] = (double)r[s] * (double)z[s];
+    v[s][1] = (double)r[s] * (double)r[s];
+  }
+  __syncthreads();  // ids
+  int epoch = 0, it = 0;
+  double sum[2], pq[1];
+  bool ok = cp_sum<2, RPT, false, true>(a, epoch++, v, sum, sh, [z0, ids, zh, nh, lost = &sh.lost](int t, int c) {
+    cp_fetch<T>(z0, ids, zh, nh, lost, t, c);
+  });
+  double rz = sum[0], beta = 0.0;
+  const double rr0 = sum[1];
+  while (ok && it < a.maxit) {
+    // p = z + beta p: the own rows' z from registers, the halo's as their owners stored it
+    const T bt = (T)beta;
+#pragma unroll
+    for (int s = 0; s < RPT; ++s) {
+      po[s] = it ? fma_t(bt, po[s], z[s]) : z[s];
+      if (whole[s]) p[tid + s * CP_NT] = po[s];
+    }
+    for (int e = tid; e < 3 * nh; e += CP_NT) ph[e] = it ? fma_t(bt, ph[e], zh[e]) : zh[e];
+    __syncthreads();
+    T q[RPT];
+    double c[RPT][1];
+#pragma unroll
+    for (int s = 0; s < RPT; ++s) {
+      // column by column as in the launch-per-iteration form
+      T acc = 0;
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        const T *pc = p + ((off[s][j / 2] >> (j % 2 ? 16 : 0)) & 0xffffu);
+        acc += A[s][3 * j] * pc[0] + A[s][3 * j + 1] * pc[1] + A[s][3 * j + 2] * pc[2];
+        // a few columns' reads at a time: all at once would not fit the registers
+        if (j % 3 == 2) asm volatile("" : "+v"(acc)::"memory");
+      }
+      q[s] = acc;
+      c[s][0] = (double)po[s] * (double)q[s];
+    }
+    ok = cp_sum<1, RPT, true, false>(a, epoch++, c, pq, sh, [](int, int) {});
+    if (!ok || !(pq[0] > 0.0)) break;  // breakdown: x as it is
+    const T al = (T)(rz / pq[0]);
+    U *const zw = it & 1 ? z0 : z1, *const zo = it & 1 ? z1 : z0;
+#pragma unroll
+    for (int s = 0; s < RPT; ++s) {
+      const int row = tid + s * CP_NT;
+      x[s] += al * po[s];
+      r[s] = r[s] - al * q[s];
+      z[s] = di[s] * r[s];
+      if (row < rows) {
+        agent_store(zw + row0 + row, B::of(z[s]));
+        agent_store(zo + row0 + row, B::EMPTY);  // all have fetched it before they posted p.q
+      }
+      v[s][0] = (double)r[s] * (double)z[s];
+      v[s][1] = (double)r[s] * (double)r[s];
+    }
+    ok = cp_sum<2, RPT, false, false>(a, epoch++, v, sum, sh, [zw, ids, zh, nh, lost = &sh.lost](int t, int c) {
+      cp_fetch<T>(zw, ids, zh, nh, lost, t, c);
+    });
+    if (!ok) break;
+    ++it;
+    beta = rz != 0.0 ? sum[0] / rz : 0.0;
+    rz = sum[0];
+    if (sum[1] <= a.rtol2 * rr0) break;
+  }
+  if (!ok) {
+    if (tid == 0) a.sc[SC_LOST] = 1.0;
+    return;
+  }
+#pragma unroll
+  for (int s = 0; s < RPT; ++s) {
+    const int row = tid + s * CP_NT;
+    if (row < rows) ((T *)a.x)[row0 + row] = x[s];
+  }
+  if (g == 0 && tid == 0) a.sc[SC_COUNT] = (double)it;
+}
+
 }  // namespace
+
+// A row to a thread (162 registers of matrix in FP64), or two in FP32.
+int coarse_pcg_max_rows(int prec) { return (prec == HPMG_F64 ? 1 : 2) * CP_NT; }
+
+size_t coarse_pcg_lds(int prec, int rows, int max_halo) {
+  return (size_t)(rows + 6 * max_halo) * prec_size(prec) + (size_t)max_halo * sizeof(int32_t);
+}
+
+// A set of slots for each of the ring and copy: two values per block of BS rows.
+size_t coarse_pcg_slots(int64_t nn) {
+  return (size_t)COARSE_PCG_COPIES * CP_RING * 2 * (size_t)((3 * nn + BS - 1) / BS);
+}
+
+hipError_t launch_coarse_pcg(int prec, const CoarsePcg &a, hipStream_t s) {
+  const size_t lds = coarse_pcg_lds(prec, a.rows, a.max_halo);
+  const int64_t n_slots = (int64_t)coarse_pcg_slots(a.nn);
+  const unsigned clear = grid_for(std::max<int64_t>(3 * a.nn, n_slots)), g = (unsigned)a.groups;
+  if (prec == HPMG_F64) {
+    k_coarse_begin<double><<<clear, BS, 0, s>>>(a, n_slots);
+    k_coarse_pcg<double, 1><<<g, CP_NT, lds, s>>>(a);
+  } else {
+    k_coarse_begin<float><<<clear, BS, 0, s>>>(a, n_slots);
+    if (a.rows <= CP_NT)
+      k_coarse_pcg<float, 1><<<g, CP_NT, lds, s>>>(a);
+    else
+      k_coarse_pcg<float, 2><<<g, CP_NT, lds, s>>>(a);
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_fcg_update(int64_t n, double *sc, int it, const double *p, const double *q, double *x,
                              const double *r, double *rn, double *partial, hipStream_t s) {
