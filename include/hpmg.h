@@ -184,7 +184,7 @@ int hpmg_external_load(hpmg_op op, const double *rho_g, const double *coords, in
 /* Alternative linearisations (Table different-storage) at u: grad_X u (9), C^-1 (6,
  * symmetric xx yy zz yz xz xy), lambda log J (1), dxi/dx (9), J - 1 (1) per point,
  * written to a caller-owned device buffer of hpmg_state_initial_bytes() bytes (FP64,
- * [tile][26][ET*Q^3], 256-byte aligned) that the operator then reads in the
+ * [tile][26][points, padded], 256-byte aligned) that the operator then reads in the
  * HPMG_INITIAL_NATIVE, HPMG_INITIAL_TUNED and HPMG_CURRENT_20 Jacobian modes (each
  * reads only its own fields); the buffer must stay allocated while they are used and
  * is not refreshed by hpmg_residual.  Fine operators only. */

@@ -146,7 +146,7 @@ int hpmg_op_create(int P, int Q, int64_t n_elem, int64_t n_nodes, const int32_t 
   op->elem_nodes = elem_nodes;
   op->mask = mask;
   op->ET = ET;
-  op->NQ = ET * Q * Q * Q;
+  op->NQ = field_stride(Q);
   op->NT = tile_threads(Q);
   op->tiles = tiles;
   int st = fill_tables(op, ex);

@@ -10,7 +10,7 @@
 //   ->  transposed derivative and interpolation in LDS  ->  element records, summed per
 //       node in a fixed order by a node-centric assembly pass (E^T, no atomics).
 //
-// Quadrature-point data are read/written as [tile][field][ET*Q^3] so each field of a
+// Quadrature-point data are read/written as [tile][field][field_stride(Q)] so each field of a
 // tile is one contiguous, coalesced sweep.  Dirichlet flags ride in the top bits of the
 // element-to-node map, so masking costs no extra memory traffic.
 #include <cmath>
@@ -27,7 +27,7 @@ template <int Q>
 struct QT {
   static constexpr int Q3 = Q * Q * Q;
   static constexpr int ET = elems_per_tile(Q);
-  static constexpr int NQ = ET * Q3;
+  static constexpr int NQ = field_stride(Q);
   static constexpr int NT = tile_threads(Q);
 };
 
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_qdata(const uint32_t *__restrict_
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sB, tab, TAB_B, Q * P, tq, NT);
   load_tables(sD, tab, TAB_D, Q * Q, tq, NT);
   load_tables(sW, tab, TAB_W, Q, tq, NT);
@@ -553,8 +553,9 @@ __device__ __forceinline__ void line_task(T *p, const T *__restrict__ M) {
 // flux from the geometry (W, dxi/dX), the 16-scalar state written to state_out when it
 // is given, non-positive or non-finite J raised in flags.
 // MODE 5: the Jacobian with the linearisation recomputed at u (T = double or float; u
-// is converted to T): the kinematics of u from the geometry at every point, then the
-// action on du as in MODE 0.
+// is converted to T): u and du go through the forward stages side by side (half the
+// barriers of one after the other, and nothing of u to keep in registers meanwhile); the
+// kinematics of u from the geometry at every point, then the action on du as in MODE 0.
 // SWEEP 1 / 2: the tile's element records leave LDS in contiguous sweeps (each store
 // instruction covers whole cache lines) with plain (1) or nontemporal (2) stores, instead
 // of three strided stores per node (0).  The two sweep kinds are separate instances: a
@@ -573,171 +574,142 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
   // Per element: v [3][Q^3] (du, then its values at the points, then the z-derivative
   // G[c][2] and the z-flux in place, then the nodal result) and G [3][2][Q^3] (the x- and
   // y-derivatives, then the x- and y-flux): 9 Q^3 scalars, so that more tiles fit in LDS.
-  constexpr int ELS = 9 * Q3;
+  // MODE 5 carries two fields, u and then du, each in frames of its own.
+  constexpr int NF = MODE == 5 ? 2 : 1, FS = 9 * Q3, ELS = NF * FS;
   __shared__ T lds[ET * ELS];
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
   const int nel = (int)((E - tile * ET) < ET ? (E - tile * ET) : ET);
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   const T *tB = tab + TAB_B, *tD = tab + TAB_D;
-  T *v = lds + (live ? el : 0) * ELS, *G = v + 3 * Q3;
+  T *v = lds + (live ? el : 0) * ELS + (NF - 1) * FS, *G = v + 3 * Q3;
   // Frame index of node q (q < P^3).
   const int qn = (q % P) + Q * ((q / P) % P) + Q2 * (q / (P * P));
   T sv[MODE == 0 ? NSTATE : 1];
   double gv[MODE == 0 ? 1 : MODE == 3 ? 1 : NGEO], hv[MODE == 0 ? 1 : NH];
-  // FI: with P == Q every stage of 3 Q^2 line tasks per element decomposes a thread's
-  // task alike (element, component, line), only the line's direction changes, and each
-  // thread has at most one such task: its line offsets are formed once here (the same
-  // arithmetic in the same order as the generic stages; measured 3-4 % faster for
-  // order 4 in FP32 and order 2 in FP64, 1 % slower for order 4 in FP64, which keeps the
-  // generic stages).
-  constexpr bool FI = (P == Q) && (ET * 3 * Q2 <= NT) && !(std::is_same<T, double>::value && P == 5);
+  // Stages over 3 Q^2 lines per element give a thread the same (element, component, line)
+  // every time, only the line's direction changes: its offsets are formed once (all orders
+  // but Q = 2, whose tile has more lines than threads).
+  constexpr int LT = ET * 3 * Q2, NL = (LT + NT - 1) / NT;
+  constexpr bool FI = NL == 1;
   const int e3 = tq / (3 * Q2), r3 = tq % (3 * Q2), c3 = r3 / Q2, ln3 = r3 % Q2;
-  const bool a3 = tq < ET * 3 * Q2 && e3 < nel;
+  const bool a3 = tq < LT && e3 < nel;
   T *const p3 = lds + (a3 ? e3 * ELS + c3 * Q3 : 0);
   const int lb0 = line_base<Q, 0, Q>(ln3), lb1 = line_base<Q, 1, Q>(ln3), lb2 = line_base<Q, 2, Q>(ln3);
-  // MODE 5 runs the forward stages twice: on u first (pass 0), keeping the kinematics of
-  // each point in registers, then, like every form, on du (pass 1).
-  T kA[3][3], ktau[6], kc = T(0);
-#pragma unroll 1
-  for (int pass = MODE == 5 ? 0 : 1; pass < 2; ++pass) {
-    if (live && q < P3) {
-      const uint32_t w = emap[e * P3 + q];
-      T x0, x1, x2;
-      if (MODE == 5 && pass == 0) {
-        const double *src = u + (int64_t)(w & EMAP_ID_MASK) * 3;
-        x0 = (T)src[0], x1 = (T)src[1], x2 = (T)src[2];
-      } else {
-        const T *src = du + (int64_t)(w & EMAP_ID_MASK) * 3;
-        x0 = src[0], x1 = src[1], x2 = src[2];
-      }
-      // u is taken whole (the residual, the recompute form's first pass); du has its
-      // constrained components zeroed
-      const uint32_t bc = (MODE == 4 || pass == 0) ? 0u : (w >> EMAP_BC_SHIFT);
-      v[qn] = (bc & 1u) ? T(0) : x0;
-      v[Q3 + qn] = ((bc >> 1) & 1u) ? T(0) : x1;
-      v[2 * Q3 + qn] = ((bc >> 2) & 1u) ? T(0) : x2;
-    }
-    if (live && (MODE != 5 || pass == 0)) {
-      if constexpr (MODE == 0) {
-        const T *s = state + tile * NSTATE * NQ + tq;
+  // f(i, v frame of the line's component, its frame in G, first offset of its x, y and z
+  // line) for the i-th of this thread's lines, for fields f0 .. NF - 1.
+  auto lines = [&](int f0, auto &&f) {
+    if constexpr (FI) {
+      if (a3)
 #pragma unroll
-        for (int f = 0; f < NSTATE; ++f) sv[f] = __builtin_nontemporal_load(s + f * NQ);
-      } else if constexpr (MODE == 3) {
-        gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W only
-        const double *h = sinit + tile * NINIT * NQ + tq;
+        for (int k = f0; k < NF; ++k) f(k, p3 + k * FS, p3 + k * FS + (3 + c3) * Q3, lb0, lb1, lb2);
+    } else {
 #pragma unroll
-        for (int f = 0; f < 9; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
+      for (int i = 0; i < NL; ++i) {
+        const int t = tq + i * NT, te = t / (3 * Q2), r = t % (3 * Q2), c = r / Q2, ln = r % Q2;
+        T *p = lds + te * ELS + c * Q3;
+        if (t < LT && te < nel)
 #pragma unroll
-        for (int f = 0; f < 10; ++f) hv[9 + f] = __builtin_nontemporal_load(h + (16 + f) * NQ);
-      } else if constexpr (MODE == 4 || MODE == 5) {
-        const double *g = geo + tile * NGEO * NQ + tq;
-#pragma unroll
-        for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
-      } else {
-        const double *g = geo + tile * NGEO * NQ + tq;
-#pragma unroll
-        for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
-        const double *h = sinit + tile * NINIT * NQ + tq;
-#pragma unroll
-        for (int f = 0; f < NH; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
+          for (int k = f0; k < NF; ++k)
+            f(i * NF + k, p + k * FS, p + k * FS + (3 + c) * Q3, line_base<Q, 0, Q>(ln), line_base<Q, 1, Q>(ln),
+              line_base<Q, 2, Q>(ln));
       }
     }
-    __syncthreads();
-    // Interpolation to the points, one direction at a time, in place.
-    if constexpr (FI) {
-      if (a3) line_task<T, P, Q, false, 1>(p3 + lb0, tB);
-    } else {
-      line_stage<T, Q, 0, P, Q, false, P, P, ET, ELS>(lds, tB, tq, NT, nel);
-    }
-    __syncthreads();
-    if constexpr (FI) {
-      if (a3) line_task<T, P, Q, false, Q>(p3 + lb1, tB);
-    } else {
-      line_stage<T, Q, 1, P, Q, false, Q, P, ET, ELS>(lds, tB, tq, NT, nel);
-    }
-    __syncthreads();
-    if constexpr (FI) {
-      if (a3) line_task<T, P, Q, false, Q2>(p3 + lb2, tB);
-    } else {
-      line_stage<T, Q, 2, P, Q, false, Q, Q, ET, ELS>(lds, tB, tq, NT, nel);
-    }
-    __syncthreads();
-    // Collocated derivative in the three directions: G[c][k] = D_k v[c] for k = 0, 1 into
-    // G, then (once every x and y line has read v) D_z v[c] in place over v[c].
-    {
-      constexpr int TASKS = 6 * Q2;
-      for (int t = tq; t < ET * TASKS; t += NT) {
-        const int te = t / TASKS, r = t % TASKS, ck = r / Q2, c = ck / 2, k = ck % 2, ln = r % Q2;
-        if (te >= nel) break;
-        const T *src = lds + te * ELS + c * Q3;
-        T *dst = lds + te * ELS + (3 + ck) * Q3;
-        T x[Q], y[Q];
-        if (k == 0) {
-          const int b0 = line_base<Q, 0, Q>(ln);
-#pragma unroll
-          for (int i = 0; i < Q; ++i) x[i] = src[b0 + i];
-          line_apply<T, Q, Q, false>(tD, x, y);
-#pragma unroll
-          for (int i = 0; i < Q; ++i) dst[b0 + i] = y[i];
-        } else {
-          const int b1 = line_base<Q, 1, Q>(ln);
-#pragma unroll
-          for (int i = 0; i < Q; ++i) x[i] = src[b1 + i * Q];
-          line_apply<T, Q, Q, false>(tD, x, y);
-#pragma unroll
-          for (int i = 0; i < Q; ++i) dst[b1 + i * Q] = y[i];
-        }
-      }
-    }
-    __syncthreads();
-    if constexpr (FI) {
-      if (a3) line_task<T, Q, Q, false, Q2>(p3 + lb2, tD);
-    } else {
-      constexpr int TASKS = 3 * Q2;
-      for (int t = tq; t < ET * TASKS; t += NT) {
-        const int te = t / TASKS, r = t % TASKS, c = r / Q2, ln = r % Q2;
-        if (te >= nel) break;
-        T *p = lds + te * ELS + c * Q3 + line_base<Q, 2, Q>(ln);
-        T x[Q], y[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) x[i] = p[i * Q2];
-        line_apply<T, Q, Q, false>(tD, x, y);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) p[i * Q2] = y[i];
-      }
-    }
-    __syncthreads();
+  };
+  if (live && q < P3) {
+    const uint32_t w = emap[e * P3 + q];
+    const T *src = du + (int64_t)(w & EMAP_ID_MASK) * 3;
+    const T x0 = src[0], x1 = src[1], x2 = src[2];
     if constexpr (MODE == 5) {
-      if (pass == 0) {
-        // the kinematics of u at this point, kept for the du pass
-        if (live) {
-          T Gu[3][3], D[3][3];
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            Gu[c][0] = G[(c * 2) * Q3 + q];
-            Gu[c][1] = G[(c * 2 + 1) * Q3 + q];
-            Gu[c][2] = v[c * Q3 + q];
-          }
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int J = 0; J < 3; ++J) D[k][J] = (T)gv[1 + k * 3 + J];
-          Kin<T> k;
-          kinematics(Gu, D, (T)mat_mu(mu0, mu_e, e), (T)mat_mu(lam0, lam_e, e), k);
-#pragma unroll
-          for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) kA[i][j] = k.A[i][j];
-#pragma unroll
-          for (int m = 0; m < 6; ++m) ktau[m] = k.tau[m];
-          kc = k.c;
-        }
-        __syncthreads();  // every point has read its gradient before du overwrites the frames
-      }
+      const double *su = u + (int64_t)(w & EMAP_ID_MASK) * 3;
+      T *vu = v - FS;
+      const double u0 = su[0], u1 = su[1], u2 = su[2];
+      vu[qn] = (T)u0;
+      vu[Q3 + qn] = (T)u1;
+      vu[2 * Q3 + qn] = (T)u2;
     }
-  }  // pass
+    // u is taken whole (the residual); du has its constrained components zeroed
+    const uint32_t bc = MODE == 4 ? 0u : (w >> EMAP_BC_SHIFT);
+    v[qn] = (bc & 1u) ? T(0) : x0;
+    v[Q3 + qn] = ((bc >> 1) & 1u) ? T(0) : x1;
+    v[2 * Q3 + qn] = ((bc >> 2) & 1u) ? T(0) : x2;
+  }
+  if (live) {
+    if constexpr (MODE == 0) {
+      const T *s = state + tile * NSTATE * NQ + tq;
+#pragma unroll
+      for (int f = 0; f < NSTATE; ++f) sv[f] = __builtin_nontemporal_load(s + f * NQ);
+    } else if constexpr (MODE == 3) {
+      gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W only
+      const double *h = sinit + tile * NINIT * NQ + tq;
+#pragma unroll
+      for (int f = 0; f < 9; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
+#pragma unroll
+      for (int f = 0; f < 10; ++f) hv[9 + f] = __builtin_nontemporal_load(h + (16 + f) * NQ);
+    } else if constexpr (MODE == 4 || MODE == 5) {
+      const double *g = geo + tile * NGEO * NQ + tq;
+#pragma unroll
+      for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
+    } else {
+      const double *g = geo + tile * NGEO * NQ + tq;
+#pragma unroll
+      for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
+      const double *h = sinit + tile * NINIT * NQ + tq;
+#pragma unroll
+      for (int f = 0; f < NH; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
+    }
+  }
+  __syncthreads();
+  // Interpolation to the points, one direction at a time, in place.
+  if constexpr (P == Q) {
+    lines(0, [&](int, T *p, T *, int l0, int, int) { line_task<T, P, Q, false, 1>(p + l0, tB); });
+    __syncthreads();
+    lines(0, [&](int, T *p, T *, int, int l1, int) { line_task<T, P, Q, false, Q>(p + l1, tB); });
+  } else {
+#pragma unroll
+    for (int k = 0; k < NF; ++k) line_stage<T, Q, 0, P, Q, false, P, P, ET, ELS>(lds + k * FS, tB, tq, NT, nel);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NF; ++k) line_stage<T, Q, 1, P, Q, false, Q, P, ET, ELS>(lds + k * FS, tB, tq, NT, nel);
+  }
+  __syncthreads();
+  // The z lines end at the points; their collocated derivative stays in registers until
+  // every x and y line has read the values.
+  T dz[NL * NF][Q];
+  lines(0, [&](int i, T *p, T *, int, int, int l2) {
+    T x[P], y[Q];
+#pragma unroll
+    for (int j = 0; j < P; ++j) x[j] = p[l2 + j * Q2];
+    line_apply<T, P, Q, false>(tB, x, y);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) p[l2 + j * Q2] = y[j];
+    line_apply<T, Q, Q, false>(tD, y, dz[i]);
+  });
+  __syncthreads();
+  // G[c][k] = D_k v[c] for k = 0, 1: each thread an x and a y line, so that no wave holds
+  // both directions at once (with the directions on neighbouring threads every wave ran
+  // both: 17 % more vector instructions at Q4).
+  lines(0, [&](int, T *p, T *g, int l0, int l1, int) {
+    T x[Q], y[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) x[j] = p[l0 + j];
+    line_apply<T, Q, Q, false>(tD, x, y);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) g[l0 + j] = y[j];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) x[j] = p[l1 + j * Q];
+    line_apply<T, Q, Q, false>(tD, x, y);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) g[Q3 + l1 + j * Q] = y[j];
+  });
+  __syncthreads();
+  // G[c][2] over v[c]
+  lines(0, [&](int i, T *p, T *, int, int, int l2) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) p[l2 + j * Q2] = dz[i][j];
+  });
+  __syncthreads();
   // Quadrature function, one thread per point, flux written over the gradient
   // (components k = 0, 1 in G, k = 2 in v).
   if (live) {
@@ -776,7 +748,22 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
         }
       jacobian_qf(Gq, A, tau, c, gv[0], mu, lam, f);
     } else if constexpr (MODE == 5) {
-      jacobian_qf(Gq, kA, ktau, kc, (T)gv[0], (T)mat_mu(mu0, mu_e, e), (T)mat_mu(lam0, lam_e, e), f);
+      const T *vu = v - FS, *Gf = G - FS;  // u's frames
+      T Gu[3][3], D[3][3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        Gu[c][0] = Gf[(c * 2) * Q3 + q];
+        Gu[c][1] = Gf[(c * 2 + 1) * Q3 + q];
+        Gu[c][2] = vu[c * Q3 + q];
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int J = 0; J < 3; ++J) D[k][J] = (T)gv[1 + k * 3 + J];
+      const T mu = (T)mat_mu(mu0, mu_e, e), lam = (T)mat_mu(lam0, lam_e, e);
+      Kin<T> k;
+      kinematics(Gu, D, mu, lam, k);
+      jacobian_qf(Gq, k.A, k.tau, k.c, (T)gv[0], mu, lam, f);
     } else if constexpr (MODE == 4) {
       double D[3][3];
 #pragma unroll
@@ -811,78 +798,36 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
   }
   __syncthreads();
   // Transposed derivative, x and y directions in place on the flux arrays.
-  {
-    constexpr int TASKS = 6 * Q2;
-    for (int t = tq; t < ET * TASKS; t += NT) {
-      const int te = t / TASKS, r = t % TASKS, ck = r / Q2, c = ck / 2, k = ck % 2, ln = r % Q2;
-      if (te >= nel) break;
-      T *p = lds + te * ELS + (3 + c * 2 + k) * Q3;
-      T x[Q], y[Q];
-      if (k == 0) {
-        const int b0 = line_base<Q, 0, Q>(ln);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) x[i] = p[b0 + i];
-        line_apply<T, Q, Q, true>(tD, x, y);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) p[b0 + i] = y[i];
-      } else {
-        const int b1 = line_base<Q, 1, Q>(ln);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) x[i] = p[b1 + i * Q];
-        line_apply<T, Q, Q, true>(tD, x, y);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) p[b1 + i * Q] = y[i];
-      }
-    }
-  }
+  lines(NF - 1, [&](int, T *, T *g, int l0, int l1, int) {
+    line_task<T, Q, Q, true, 1>(g + l0, tD);
+    line_task<T, Q, Q, true, Q>(g + Q3 + l1, tD);
+  });
   __syncthreads();
   // z direction: h = D_z^T f_z + (x and y parts), then the first transposed
   // interpolation stage (B_z^T, Q -> P) in registers; the result goes to v, over the
   // z-flux line it was formed from.
-  if constexpr (FI) {
-    if (a3) {
-      const T *fxy = p3 + (3 + c3) * Q3 + lb2;
-      T *o = p3 + lb2;
-      T x[Q], y[Q], z[P];
+  lines(NF - 1, [&](int, T *p, T *g, int, int, int l2) {
+    const T *fxy = g + l2;
+    T *o = p + l2;
+    T x[Q], y[Q], z[P];
 #pragma unroll
-      for (int i = 0; i < Q; ++i) x[i] = o[i * Q2];
-      line_apply<T, Q, Q, true>(tD, x, y);
+    for (int i = 0; i < Q; ++i) x[i] = o[i * Q2];
+    line_apply<T, Q, Q, true>(tD, x, y);
 #pragma unroll
-      for (int i = 0; i < Q; ++i) y[i] += fxy[i * Q2] + fxy[Q3 + i * Q2];
-      line_apply<T, Q, P, true>(tB, y, z);
+    for (int i = 0; i < Q; ++i) y[i] += fxy[i * Q2] + fxy[Q3 + i * Q2];
+    line_apply<T, Q, P, true>(tB, y, z);
 #pragma unroll
-      for (int i = 0; i < P; ++i) o[i * Q2] = z[i];
-    }
-  } else {
-    constexpr int TASKS = 3 * Q2;
-    for (int t = tq; t < ET * TASKS; t += NT) {
-      const int te = t / TASKS, r = t % TASKS, c = r / Q2, ln = r % Q2;
-      if (te >= nel) break;
-      const int b2 = line_base<Q, 2, Q>(ln);
-      const T *fxy = lds + te * ELS + (3 + c * 2) * Q3 + b2;
-      T *o = lds + te * ELS + c * Q3 + b2;
-      T x[Q], y[Q], z[P];
-#pragma unroll
-      for (int i = 0; i < Q; ++i) x[i] = o[i * Q2];
-      line_apply<T, Q, Q, true>(tD, x, y);
-#pragma unroll
-      for (int i = 0; i < Q; ++i) y[i] += fxy[i * Q2] + fxy[Q3 + i * Q2];
-      line_apply<T, Q, P, true>(tB, y, z);
-#pragma unroll
-      for (int i = 0; i < P; ++i) o[i * Q2] = z[i];
-    }
-  }
+    for (int i = 0; i < P; ++i) o[i * Q2] = z[i];
+  });
   __syncthreads();
-  if constexpr (FI) {
-    if (a3) line_task<T, Q, P, true, Q>(p3 + lb1, tB);
+  if constexpr (P == Q) {
+    lines(NF - 1, [&](int, T *p, T *, int, int l1, int) { line_task<T, Q, P, true, Q>(p + l1, tB); });
+    __syncthreads();
+    lines(NF - 1, [&](int, T *p, T *, int l0, int, int) { line_task<T, Q, P, true, 1>(p + l0, tB); });
   } else {
-    line_stage<T, Q, 1, Q, P, true, Q, P, ET, ELS>(lds, tB, tq, NT, nel);
-  }
-  __syncthreads();
-  if constexpr (FI) {
-    if (a3) line_task<T, Q, P, true, 1>(p3 + lb0, tB);
-  } else {
-    line_stage<T, Q, 0, Q, P, true, P, P, ET, ELS>(lds, tB, tq, NT, nel);
+    line_stage<T, Q, 1, Q, P, true, Q, P, ET, ELS>(lds + (NF - 1) * FS, tB, tq, NT, nel);
+    __syncthreads();
+    line_stage<T, Q, 0, Q, P, true, P, P, ET, ELS>(lds + (NF - 1) * FS, tB, tq, NT, nel);
   }
   __syncthreads();
   if constexpr (SWEEP > 0) {
@@ -893,9 +838,9 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
       const int r = d / 3, c = d - 3 * r, te = r / P3, a = r - te * P3;
       const int an = (a % P) + Q * ((a / P) % P) + Q2 * (a / (P * P));
       if constexpr (SWEEP == 1)
-        o[d] = lds[te * ELS + c * Q3 + an];
+        o[d] = lds[te * ELS + (NF - 1) * FS + c * Q3 + an];
       else
-        __builtin_nontemporal_store(lds[te * ELS + c * Q3 + an], o + d);
+        __builtin_nontemporal_store(lds[te * ELS + (NF - 1) * FS + c * Q3 + an], o + d);
     }
   } else if (live && q < P3) {
     T *o = ev + ((int64_t)e * P3 + q) * 3;
@@ -920,7 +865,7 @@ void lines_launch(unsigned tiles, hipStream_t s, bool keep, A... a) {
 }
 
 // ------------------------------------------------------------------------------------
-// Alternative linearisations at u, per point, [tile][26][ET*Q^3]: grad_X u (9),
+// Alternative linearisations at u, per point, [tile][26][field_stride]: grad_X u (9),
 // C^-1 (6), lambda log J (1), dxi/dx (9), J - 1 (1).  With the constant W and
 // grad_X xi, fields 0-8 are the 19-scalar initial-configuration "native" form, 0-15 the
 // 26-scalar "tuned" form; fields 0-8 and 16-25 with W are the 20-scalar current-
@@ -939,7 +884,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_state_initial(
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sB, tab, TAB_B, Q * P, tq, NT);
   load_tables(sD, tab, TAB_D, Q * Q, tq, NT);
   T *a = lds + (live ? el : 0) * S0, *b = lds + ET * S0 + (live ? el : 0) * S0;
@@ -997,7 +942,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_body_load(const double *__restric
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sB, tab, TAB_B, Q * P, tq, NT);
   T *a = lds + (live ? el : 0) * Q3, *b = lds + ET * Q3 + (live ? el : 0) * Q3;
   if (live) b[q] = geo[tile * NGEO * NQ + tq];  // W
@@ -1094,7 +1039,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_diagonal(
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sBB, tab, TAB_BB, Q * P, tq, NT);
   load_tables(sBG, tab, TAB_BG, Q * P, tq, NT);
   load_tables(sGG, tab, TAB_GG, Q * P, tq, NT);
@@ -1430,7 +1375,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_energy(const uint32_t *__restrict
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sB, tab, TAB_B, Q * P, tq, NT);
   load_tables(sD, tab, TAB_D, Q * Q, tq, NT);
   T *a = lds + (live ? el : 0) * S0, *b = lds + ET * S0 + (live ? el : 0) * S1;
@@ -1488,7 +1433,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_vjp(
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
+  const bool live = tq < ET * Q3 && e < E;
   load_tables(sB, tab, TAB_B, Q * P, tq, NT);
   load_tables(sD, tab, TAB_D, Q * Q, tq, NT);
   T *a = lds + (live ? el : 0) * S0, *b = lds + ET * S0 + (live ? el : 0) * S1;
