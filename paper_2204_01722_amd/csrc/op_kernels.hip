@@ -114,34 +114,6 @@ __device__ __forceinline__ void grad_q(const T *in, const T *sD, int q, T (&G)[N
   }
 }
 
-// Transposed collocated derivative summed over directions: out[c][q] =
-// sum_k sum_j D[j][q_k] f[c][k][.. j ..], f laid out [3][3][Q^3].
-template <typename T, int Q>
-__device__ __forceinline__ void grad_t_q(const T *f, const T *sD, int q, T *out, bool live) {
-  constexpr int Q3 = Q * Q * Q;
-  if (!live || q >= Q3) return;
-  const int q1 = q % Q, q2 = (q / Q) % Q, q3 = q / (Q * Q);
-  T d1[Q], d2[Q], d3[Q];
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    d1[j] = sD[j * Q + q1];
-    d2[j] = sD[j * Q + q2];
-    d3[j] = sD[j * Q + q3];
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    T acc = 0;
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      acc += d1[j] * f[(c * 3 + 0) * Q3 + j + Q * (q2 + Q * q3)];
-      acc += d2[j] * f[(c * 3 + 1) * Q3 + q1 + Q * (j + Q * q3)];
-      acc += d3[j] * f[(c * 3 + 2) * Q3 + q1 + Q * (q2 + Q * j)];
-    }
-    asm volatile("" : "+v"(acc)::"memory");
-    out[c * Q3 + q] = acc;
-  }
-}
-
 template <typename T>
 __device__ __forceinline__ T det3(const T (&m)[3][3]) {
   return m[0][0] * (m[1][1] * m[2][2] - m[1][2] * m[2][1]) -
@@ -543,6 +515,40 @@ __device__ __forceinline__ void line_task(T *p, const T *__restrict__ M) {
   for (int i = 0; i < NO; ++i) p[i * ST] = y[i];
 }
 
+// Element records [e][a][c] out of the tile's LDS frames (component c of element te at
+// f + te * els + c * Q^3, nodes at their frame index).  SWEEP 1 / 2: contiguous sweeps over
+// the tile's run of records (each store instruction covers whole cache lines) with plain
+// (1) or nontemporal (2) stores; 0: three strided stores per node.  The two sweep kinds are
+// separate instances: a run-time choice lets the compiler merge both stores into a plain
+// one.
+template <typename T, int P, int Q, int SWEEP>
+__device__ __forceinline__ void store_tile_records(T *__restrict__ ev, int64_t tile, int nel, const T *f, int els) {
+  constexpr int Q2 = Q * Q, Q3 = Q2 * Q, P3 = P * P * P, ET = QT<Q>::ET, NT = QT<Q>::NT;
+  const int tq = threadIdx.x;
+  if constexpr (SWEEP > 0) {
+    T *o = ev + tile * (int64_t)(ET * P3 * 3);
+    const int nd = nel * P3 * 3;
+    for (int d = tq; d < nd; d += NT) {
+      const int r = d / 3, c = d - 3 * r, te = r / P3, a = r - te * P3;
+      const int an = (a % P) + Q * ((a / P) % P) + Q2 * (a / (P * P));
+      if constexpr (SWEEP == 1)
+        o[d] = f[te * els + c * Q3 + an];
+      else
+        __builtin_nontemporal_store(f[te * els + c * Q3 + an], o + d);
+    }
+  } else {
+    const int el = tq / Q3, q = tq % Q3;
+    if (el < nel && q < P3) {
+      const T *v = f + el * els + (q % P) + Q * ((q / P) % P) + Q2 * (q / (P * P));
+      const T y0 = v[0], y1 = v[Q3], y2 = v[2 * Q3];
+      T *o = ev + ((tile * ET + el) * P3 + q) * 3;
+      o[0] = y0;
+      o[1] = y1;
+      o[2] = y2;
+    }
+  }
+}
+
 // MODE 0: the 16-scalar current-configuration state (sqrt(W) dxi/dx, tau, lambda log J;
 // T = double or float).
 // MODE 1 / 2: the initial-configuration forms, 19 / 26 scalars (geometry W, grad_X xi
@@ -556,17 +562,25 @@ __device__ __forceinline__ void line_task(T *p, const T *__restrict__ M) {
 // is converted to T): u and du go through the forward stages side by side (half the
 // barriers of one after the other, and nothing of u to keep in registers meanwhile); the
 // kinematics of u from the geometry at every point, then the action on du as in MODE 0.
-// SWEEP 1 / 2: the tile's element records leave LDS in contiguous sweeps (each store
-// instruction covers whole cache lines) with plain (1) or nontemporal (2) stores, instead
-// of three strided stores per node (0).  The two sweep kinds are separate instances: a
-// run-time choice lets the compiler merge both stores into a plain one.
+// MODE 6 / 7: the adjoint (vector-Jacobian product; du is the cotangent w of the masked
+// residual) from the 16-scalar state / recomputed at u (T = double or float).  With mub or
+// lamb given, the parameter gradients of every element: the point values are two more
+// frames, summed line by line along x, z and y in the transposed stages by the threads
+// counted from the last, most of which have no line of their own there.  With a thread per
+// point, all contractions out of LDS (two workgroups per compute unit) and one thread an
+// element summing the parameters, the FP64 product took 165 us on 20^3 Q4 elements and 53.5
+// on 23^3 Q3 ones, assembly included; this form 46.7 and 38.0 (recomputed 180 -> 61 and
+// 56 -> 49; MODE 7 is held to 128 registers for four waves per SIMD, 63 and 51 without).
+// SWEEP: how the records are stored (store_tile_records).
 template <typename T, int P, int Q, int MODE, int SWEEP>
-__global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
+__global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines(
     const uint32_t *__restrict__ emap, const T *__restrict__ du, const T *__restrict__ state,
     const double *__restrict__ geo, const double *__restrict__ sinit,
     const T *__restrict__ tab, double mu0, double lam0, const double *__restrict__ mu_e,
     const double *__restrict__ lam_e, T *__restrict__ ev, int64_t E, const double *__restrict__ stop,
-    double *__restrict__ state_out, unsigned *__restrict__ flags, const double *__restrict__ u) {
+    double *__restrict__ state_out, unsigned *__restrict__ flags, const double *__restrict__ u,
+    double *__restrict__ mub, double *__restrict__ lamb) {
+  constexpr bool STATE = MODE == 0 || MODE == 6, TWO = MODE == 5 || MODE == 7, VJP = MODE == 6 || MODE == 7;
   constexpr int NH = MODE == 2 ? 16 : MODE == 3 ? 19 : 9;
   static_assert(MODE != 4 || std::is_same<T, double>::value, "the residual form is FP64");
   if (stop && *stop != 0.0) return;  // a stopped PCG (uniform over the grid)
@@ -574,8 +588,9 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
   // Per element: v [3][Q^3] (du, then its values at the points, then the z-derivative
   // G[c][2] and the z-flux in place, then the nodal result) and G [3][2][Q^3] (the x- and
   // y-derivatives, then the x- and y-flux): 9 Q^3 scalars, so that more tiles fit in LDS.
-  // MODE 5 carries two fields, u and then du, each in frames of its own.
-  constexpr int NF = MODE == 5 ? 2 : 1, FS = 9 * Q3, ELS = NF * FS;
+  // MODES 5 and 7 carry two fields, u and then du, each in frames of its own; MODES 6 and 7
+  // end with the two parameter frames.
+  constexpr int NF = TWO ? 2 : 1, FS = 9 * Q3, PS = NF * FS, ELS = PS + (VJP ? 2 * Q3 : 0);
   __shared__ T lds[ET * ELS];
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
@@ -586,8 +601,9 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
   T *v = lds + (live ? el : 0) * ELS + (NF - 1) * FS, *G = v + 3 * Q3;
   // Frame index of node q (q < P^3).
   const int qn = (q % P) + Q * ((q / P) % P) + Q2 * (q / (P * P));
-  T sv[MODE == 0 ? NSTATE : 1];
-  double gv[MODE == 0 ? 1 : MODE == 3 ? 1 : NGEO], hv[MODE == 0 ? 1 : NH];
+  T sv[STATE ? NSTATE : 1];
+  double gv[STATE || MODE == 3 ? 1 : NGEO], hv[STATE ? 1 : NH];
+  const bool par = VJP && (mub || lamb);
   // Stages over 3 Q^2 lines per element give a thread the same (element, component, line)
   // every time, only the line's direction changes: its offsets are formed once (all orders
   // but Q = 2, whose tile has more lines than threads).
@@ -621,7 +637,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
     const uint32_t w = emap[e * P3 + q];
     const T *src = du + (int64_t)(w & EMAP_ID_MASK) * 3;
     const T x0 = src[0], x1 = src[1], x2 = src[2];
-    if constexpr (MODE == 5) {
+    if constexpr (TWO) {
       const double *su = u + (int64_t)(w & EMAP_ID_MASK) * 3;
       T *vu = v - FS;
       const double u0 = su[0], u1 = su[1], u2 = su[2];
@@ -636,10 +652,11 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
     v[2 * Q3 + qn] = ((bc >> 2) & 1u) ? T(0) : x2;
   }
   if (live) {
-    if constexpr (MODE == 0) {
+    if constexpr (STATE) {
       const T *s = state + tile * NSTATE * NQ + tq;
 #pragma unroll
       for (int f = 0; f < NSTATE; ++f) sv[f] = __builtin_nontemporal_load(s + f * NQ);
+      if (par) gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W
     } else if constexpr (MODE == 3) {
       gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W only
       const double *h = sinit + tile * NINIT * NQ + tq;
@@ -647,7 +664,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
       for (int f = 0; f < 9; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
 #pragma unroll
       for (int f = 0; f < 10; ++f) hv[9 + f] = __builtin_nontemporal_load(h + (16 + f) * NQ);
-    } else if constexpr (MODE == 4 || MODE == 5) {
+    } else if constexpr (MODE == 4 || TWO) {
       const double *g = geo + tile * NGEO * NQ + tq;
 #pragma unroll
       for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
@@ -747,7 +764,29 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
           tau[sym_index(i, j)] = mu * (hv[i * 3 + j] + hv[j * 3 + i] + hh) + (i == j ? c : 0.0);
         }
       jacobian_qf(Gq, A, tau, c, gv[0], mu, lam, f);
-    } else if constexpr (MODE == 5) {
+    } else if constexpr (MODE == 6) {
+      // the weight rides in the scaled dxi/dx: M below is sqrt(W) w's gradient
+      T A[3][3], tau[6], M[3][3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) A[k][j] = sv[k * 3 + j];
+#pragma unroll
+      for (int m = 0; m < 6; ++m) tau[m] = sv[9 + m];
+      const T c = sv[15], mu = (T)mat_mu(mu0, mu_e, e), lam = (T)mat_mu(lam0, lam_e, e);
+      adjoint_qf(Gq, A, tau, c, T(1), mu, lam, f, M);
+      if (par) {
+        // tau = 2 mu e + c I and c = lambda log J
+        const T sw = (T)sqrt(gv[0]);
+        T d = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) d += M[i][j] * (tau[sym_index(i, j)] - (i == j ? c : T(0)));
+        lds[el * ELS + PS + q] = sw * (d / mu);
+        lds[el * ELS + PS + Q3 + q] = sw * (T)((double)c / (double)lam) * (M[0][0] + M[1][1] + M[2][2]);
+      }
+    } else if constexpr (TWO) {
       const T *vu = v - FS, *Gf = G - FS;  // u's frames
       T Gu[3][3], D[3][3];
 #pragma unroll
@@ -763,7 +802,24 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
       const T mu = (T)mat_mu(mu0, mu_e, e), lam = (T)mat_mu(lam0, lam_e, e);
       Kin<T> k;
       kinematics(Gu, D, mu, lam, k);
-      jacobian_qf(Gq, k.A, k.tau, k.c, (T)gv[0], mu, lam, f);
+      if constexpr (MODE == 5) {
+        jacobian_qf(Gq, k.A, k.tau, k.c, (T)gv[0], mu, lam, f);
+      } else {
+        T M[3][3];
+        const T W = (T)gv[0];
+        adjoint_qf(Gq, k.A, k.tau, k.c, W, mu, lam, f, M);
+        if (par) {
+          T d = 0;
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+              d += M[i][j] * (k.H[i][j] + k.H[j][i] + k.H[i][0] * k.H[j][0] + k.H[i][1] * k.H[j][1] +
+                              k.H[i][2] * k.H[j][2]);
+          lds[el * ELS + PS + q] = W * d;
+          lds[el * ELS + PS + Q3 + q] = W * (T)k.logJ * (M[0][0] + M[1][1] + M[2][2]);
+        }
+      }
     } else if constexpr (MODE == 4) {
       double D[3][3];
 #pragma unroll
@@ -797,11 +853,27 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
     }
   }
   __syncthreads();
+  // Sums of the parameter frames along one direction: f(frame of the parameter, element,
+  // parameter, line) for `lines` lines of each.
+  auto param_lines = [&](int lines, auto &&f) {
+    if (par)
+      for (int t = NT - 1 - tq; t < 2 * nel * lines; t += NT) {
+        const int te = t / (2 * lines), r = t % (2 * lines), k = r / lines;
+        f(lds + te * ELS + PS + k * Q3, te, k, r % lines);
+      }
+  };
+  auto line_sum = [&](const T *p, int step) {
+    T t = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) t += p[i * step];
+    return t;
+  };
   // Transposed derivative, x and y directions in place on the flux arrays.
   lines(NF - 1, [&](int, T *, T *g, int l0, int l1, int) {
     line_task<T, Q, Q, true, 1>(g + l0, tD);
     line_task<T, Q, Q, true, Q>(g + Q3 + l1, tD);
   });
+  if constexpr (VJP) param_lines(Q2, [&](T *p, int, int, int ln) { p[ln * Q] = line_sum(p + ln * Q, 1); });
   __syncthreads();
   // z direction: h = D_z^T f_z + (x and y parts), then the first transposed
   // interpolation stage (B_z^T, Q -> P) in registers; the result goes to v, over the
@@ -819,7 +891,13 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
 #pragma unroll
     for (int i = 0; i < P; ++i) o[i * Q2] = z[i];
   });
+  if constexpr (VJP) param_lines(Q, [&](T *p, int, int, int ln) { p[ln * Q] = line_sum(p + ln * Q, Q2); });
   __syncthreads();
+  if constexpr (VJP)
+    param_lines(1, [&](T *p, int te, int k, int) {
+      double *o = k ? lamb : mub;
+      if (o) o[tile * ET + te] = (double)line_sum(p, Q);
+    });
   if constexpr (P == Q) {
     lines(NF - 1, [&](int, T *p, T *, int, int l1, int) { line_task<T, Q, P, true, Q>(p + l1, tB); });
     __syncthreads();
@@ -830,25 +908,7 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_jacobian_lines(
     line_stage<T, Q, 0, Q, P, true, P, P, ET, ELS>(lds + (NF - 1) * FS, tB, tq, NT, nel);
   }
   __syncthreads();
-  if constexpr (SWEEP > 0) {
-    // records [e][a][c] of the tile's elements are one contiguous run of nel P^3 3 values
-    T *o = ev + tile * (int64_t)(ET * P3 * 3);
-    const int nd = nel * P3 * 3;
-    for (int d = tq; d < nd; d += NT) {
-      const int r = d / 3, c = d - 3 * r, te = r / P3, a = r - te * P3;
-      const int an = (a % P) + Q * ((a / P) % P) + Q2 * (a / (P * P));
-      if constexpr (SWEEP == 1)
-        o[d] = lds[te * ELS + (NF - 1) * FS + c * Q3 + an];
-      else
-        __builtin_nontemporal_store(lds[te * ELS + (NF - 1) * FS + c * Q3 + an], o + d);
-    }
-  } else if (live && q < P3) {
-    T *o = ev + ((int64_t)e * P3 + q) * 3;
-    const T y0 = v[qn], y1 = v[Q3 + qn], y2 = v[2 * Q3 + qn];
-    o[0] = y0;
-    o[1] = y1;
-    o[2] = y2;
-  }
+  store_tile_records<T, P, Q, SWEEP>(ev, tile, nel, lds + (NF - 1) * FS, ELS);
 }
 
 // Launches k_jacobian_lines with the record-store form for its order, precision and size.
@@ -1024,82 +1084,126 @@ __global__ void k_traction_load(const double *__restrict__ X, const int32_t *__r
 // (from the stored sqrt(W) A the weight comes out of the products itself)
 // (the Jacobian map with G = e_i grad(phi)^T); the node value is
 //   sum_q sum_kl K^(i)_kl dphi/dxi_k dphi/dxi_l,
-// a tensor product of the 1D elementwise tables B*B, B*G, G*G, contracted in three
-// transposed 1D stages for each of the six (k, l) pairs.
+// a tensor product of the 1D elementwise tables B*B, B*G, G*G.  The six (k, l) pairs need
+// six z and six y contractions, but only three tables occur along x (G*G for 00, B*G for
+// 01 and 02, B*B for the rest), so the y stage sums the pairs that share one and the x
+// stage runs three: 375 multiply-adds a line of each component at P = Q = 5 and three
+// barriers after the point stage.  Line tasks as in k_jacobian_lines, a task taking all
+// pairs of its line so that the tables stay in scalar registers.  One thread per point and
+// pair, with every contraction's operands read from LDS, took 130-147 us for 25^3 Q4
+// elements in FP64 (bound by LDS); this form 64-72, of which the 250 MB of state take 44.
 // ------------------------------------------------------------------------------------
-template <typename T, int P, int Q>
+// y += M^T x, M [NI][NO].
+template <typename T, int NI, int NO>
+__device__ __forceinline__ void line_add_t(const T *__restrict__ M, const T (&x)[NI], T (&y)[NO]) {
+#pragma unroll
+  for (int o = 0; o < NO; ++o)
+#pragma unroll
+    for (int i = 0; i < NI; ++i) y[o] += M[i * NO + o] * x[i];
+}
+
+template <typename T, int P, int Q, int SWEEP>
 __global__ __launch_bounds__(QT<Q>::NT) void k_diagonal(
-    const uint32_t *__restrict__ emap, const T *__restrict__ state, const T *__restrict__ tab,
-    double mu0, double lam0, const double *__restrict__ mu_e, const double *__restrict__ lam_e,
-    T *__restrict__ ev, int64_t E) {
-  constexpr int Q3 = QT<Q>::Q3, ET = QT<Q>::ET, NQ = QT<Q>::NQ, NT = QT<Q>::NT, P3 = P * P * P;
-  constexpr int S0 = 3 * Q3, S1 = 3 * Q3;
-  __shared__ T sBB[Q * P], sBG[Q * P], sGG[Q * P];
-  __shared__ T lds[ET * (S0 + S1)];
+    const T *__restrict__ state, const T *__restrict__ tab, double mu0, double lam0,
+    const double *__restrict__ mu_e, const double *__restrict__ lam_e, T *__restrict__ ev, int64_t E) {
+  constexpr int Q2 = Q * Q, Q3 = Q2 * Q, ET = QT<Q>::ET, NQ = QT<Q>::NQ, NT = QT<Q>::NT, P3 = P * P * P;
+  constexpr int ELS = 18 * Q3;  // per element: frame 3 p + i of pair p, component i
+  __shared__ T lds[ET * ELS];
   const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
   const int64_t tile = xcd_tile();
   const int64_t e = tile * ET + el;
+  const int nel = (int)((E - tile * ET) < ET ? (E - tile * ET) : ET);
   const bool live = tq < ET * Q3 && e < E;
-  load_tables(sBB, tab, TAB_BB, Q * P, tq, NT);
-  load_tables(sBG, tab, TAB_BG, Q * P, tq, NT);
-  load_tables(sGG, tab, TAB_GG, Q * P, tq, NT);
-  T *a = lds + (live ? el : 0) * S0, *b = lds + ET * S0 + (live ? el : 0) * S1;
-  T K[3][6];  // [component][pair]
+  const T *tBB = tab + TAB_BB, *tBG = tab + TAB_BG, *tGG = tab + TAB_GG;
   if (live) {
     T A[3][3], tau[6];
     const T *s = state + tile * NSTATE * NQ + tq;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
-      for (int j = 0; j < 3; ++j) A[k][j] = s[(k * 3 + j) * NQ];
+      for (int j = 0; j < 3; ++j) A[k][j] = __builtin_nontemporal_load(s + (k * 3 + j) * NQ);
 #pragma unroll
-    for (int m = 0; m < 6; ++m) tau[m] = s[(9 + m) * NQ];
-    const T c = s[15 * NQ], W = T(1);  // the weight is in the scaled dxi/dx
+    for (int m = 0; m < 6; ++m) tau[m] = __builtin_nontemporal_load(s + (9 + m) * NQ);
+    const T c = __builtin_nontemporal_load(s + 15 * NQ);  // the weight is in the scaled dxi/dx
     const T mu = (T)mat_mu(mu0, mu_e, e), lam = (T)mat_mu(lam0, lam_e, e);
-    T AT[3][3];  // (A tau)
+    T AT[3][3];  // A tau
+#pragma unroll
     for (int k = 0; k < 3; ++k)
+#pragma unroll
       for (int j = 0; j < 3; ++j)
         AT[k][j] = A[k][0] * tau[sym_index(0, j)] + A[k][1] * tau[sym_index(1, j)] + A[k][2] * tau[sym_index(2, j)];
-    const int pk[6] = {0, 1, 2, 1, 0, 0}, pl[6] = {0, 1, 2, 2, 2, 1};
+    constexpr int pk[6] = {0, 1, 2, 1, 0, 0}, pl[6] = {0, 1, 2, 2, 2, 1};
+    T *K = lds + el * ELS + q;
 #pragma unroll
     for (int p = 0; p < 6; ++p) {
       const int k = pk[p], l = pl[p];
       const T m1 = AT[k][0] * A[l][0] + AT[k][1] * A[l][1] + AT[k][2] * A[l][2];
       const T m2 = A[k][0] * A[l][0] + A[k][1] * A[l][1] + A[k][2] * A[l][2];
-      const T sc = (k == l) ? W : T(2) * W;
+      const T sc = (k == l) ? T(1) : T(2);
 #pragma unroll
-      for (int i = 0; i < 3; ++i) K[i][p] = sc * (m1 + (mu - c) * m2 + (lam + mu - c) * A[k][i] * A[l][i]);
+      for (int i = 0; i < 3; ++i)
+        K[(3 * p + i) * Q3] = sc * (m1 + (mu - c) * m2 + (lam + mu - c) * A[k][i] * A[l][i]);
     }
   }
-  T acc[3] = {0, 0, 0};
-  const int pk[6] = {0, 1, 2, 1, 0, 0}, pl[6] = {0, 1, 2, 2, 2, 1};
+  __syncthreads();
+  // z lines, in place (pair order 00, 11, 22, 12, 02, 01)
+  for (int t = tq; t < ET * 3 * Q2; t += NT) {
+    const int te = t / (3 * Q2), r = t % (3 * Q2), i = r / Q2;
+    if (te >= nel) break;
+    T *f = lds + te * ELS + i * Q3 + line_base<Q, 2, Q>(r % Q2);
 #pragma unroll
-  for (int p = 0; p < 6; ++p) {
-    if (live) {
-#pragma unroll
-      for (int i = 0; i < 3; ++i) b[i * Q3 + q] = K[i][p];
-    }
-    __syncthreads();
-    const int k = pk[p], l = pl[p];
-    const T *t1 = (k == 0 && l == 0) ? sGG : (k == 0 || l == 0) ? sBG : sBB;
-    const T *t2 = (k == 1 && l == 1) ? sGG : (k == 1 || l == 1) ? sBG : sBB;
-    const T *t3 = (k == 2 && l == 2) ? sGG : (k == 2 || l == 2) ? sBG : sBB;
-    stage<T, Q, Q, Q, 2, P, true, 3>(b, a, t3, q, live);
-    __syncthreads();
-    stage<T, Q, Q, P, 1, P, true, 3>(a, b, t2, q, live);
-    __syncthreads();
-    stage<T, Q, P, P, 0, P, true, 3>(b, a, t1, q, live);
-    __syncthreads();
-    if (live && q < P3) {
-#pragma unroll
-      for (int i = 0; i < 3; ++i) acc[i] += a[i * P3 + q];
-    }
+    for (int p = 0; p < 6; ++p)
+      line_task<T, Q, P, true, Q2>(f + 3 * p * Q3, p == 2 ? tGG : p == 3 || p == 4 ? tBG : tBB);
   }
-  if (live && q < P3) {
-    T *p = ev + ((int64_t)e * P3 + q) * 3;
+  __syncthreads();
+  // y lines: the sums of the pairs by their x table, into the frames of pairs 0, 1 and 2
+  for (int t = tq; t < ET * 3 * Q * P; t += NT) {
+    const int te = t / (3 * Q * P), r = t % (3 * Q * P), i = r / (Q * P);
+    if (te >= nel) break;
+    T *f = lds + te * ELS + i * Q3 + line_base<Q, 1, Q>(r % (Q * P));
+    T y[3][P];
+    auto add = [&](int p, const T *M, T (&o)[P]) {
+      T x[Q];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) p[c] = acc[c];
+      for (int j = 0; j < Q; ++j) x[j] = f[3 * p * Q3 + j * Q];
+      line_add_t<T, Q, P>(M, x, o);
+    };
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+#pragma unroll
+      for (int o = 0; o < P; ++o) y[g][o] = T(0);
+    add(0, tBB, y[0]);
+    add(4, tBB, y[1]);
+    add(5, tBG, y[1]);
+    add(1, tGG, y[2]);
+    add(2, tBB, y[2]);
+    add(3, tBG, y[2]);
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+#pragma unroll
+      for (int o = 0; o < P; ++o) f[3 * g * Q3 + o * Q] = y[g][o];
   }
+  __syncthreads();
+  // x lines
+  for (int t = tq; t < ET * 3 * P * P; t += NT) {
+    const int te = t / (3 * P * P), r = t % (3 * P * P), i = r / (P * P);
+    if (te >= nel) break;
+    T *f = lds + te * ELS + i * Q3 + line_base<Q, 0, P>(r % (P * P));
+    T y[P];
+#pragma unroll
+    for (int o = 0; o < P; ++o) y[o] = T(0);
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      T x[Q];
+#pragma unroll
+      for (int j = 0; j < Q; ++j) x[j] = f[3 * g * Q3 + j];
+      line_add_t<T, Q, P>(g == 0 ? tGG : g == 1 ? tBG : tBB, x, y);
+    }
+#pragma unroll
+    for (int o = 0; o < P; ++o) f[o] = y[o];
+  }
+  __syncthreads();
+  store_tile_records<T, P, Q, SWEEP>(ev, tile, nel, lds, ELS);
 }
 
 
@@ -1416,141 +1520,6 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_energy(const uint32_t *__restrict
   }
 }
 
-// ------------------------------------------------------------------------------------
-// a16: adjoint (vector-Jacobian product) of the masked residual.
-// ------------------------------------------------------------------------------------
-template <typename T, int P, int Q, bool STORED>
-__global__ __launch_bounds__(QT<Q>::NT) void k_vjp(
-    const uint32_t *__restrict__ emap, const double *__restrict__ u, const T *__restrict__ w,
-    const double *__restrict__ geo, const T *__restrict__ state, const T *__restrict__ tab,
-    double mu0, double lam0, const double *__restrict__ mu_e, const double *__restrict__ lam_e,
-    T *__restrict__ ev, double *__restrict__ mub, double *__restrict__ lamb, int64_t E) {
-  constexpr int Q3 = QT<Q>::Q3, ET = QT<Q>::ET, NQ = QT<Q>::NQ, NT = QT<Q>::NT, P3 = P * P * P;
-  constexpr int NC = STORED ? 3 : 6;
-  constexpr int S0 = 9 * Q3, S1 = 6 * Q3;
-  __shared__ T sB[Q * P], sD[Q * Q];
-  __shared__ T lds[ET * (S0 + S1)];
-  const int tq = threadIdx.x, el = tq / Q3, q = tq % Q3;
-  const int64_t tile = xcd_tile();
-  const int64_t e = tile * ET + el;
-  const bool live = tq < ET * Q3 && e < E;
-  load_tables(sB, tab, TAB_B, Q * P, tq, NT);
-  load_tables(sD, tab, TAB_D, Q * Q, tq, NT);
-  T *a = lds + (live ? el : 0) * S0, *b = lds + ET * S0 + (live ? el : 0) * S1;
-  if (live && q < P3) {
-    const uint32_t wd = emap[e * P3 + q];
-    const uint32_t node = wd & EMAP_ID_MASK;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      a[c * P3 + q] = ((wd >> (EMAP_BC_SHIFT + c)) & 1u) ? T(0) : w[(int64_t)node * 3 + c];
-      if (!STORED) a[(3 + c) * P3 + q] = (T)u[(int64_t)node * 3 + c];
-    }
-  }
-  __syncthreads();
-  interp<T, P, Q, NC>(a, b, sB, q, live);
-  T pm = 0, pl = 0;
-  if (live) {
-    T G[NC][3], C[3][3], A[3][3], tau[6], c, W;
-    grad_q<T, Q, NC>(b, sD, q, G);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) C[i][k] = G[i][k];
-    const T mu = (T)mat_mu(mu0, mu_e, e), lam = (T)mat_mu(lam0, lam_e, e);
-    T twoe[6];
-    double logJ;
-    if (STORED) {
-      const T *s = state + tile * NSTATE * NQ + tq;
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) A[k][j] = s[(k * 3 + j) * NQ];
-#pragma unroll
-      for (int m = 0; m < 6; ++m) tau[m] = s[(9 + m) * NQ];
-      c = s[15 * NQ];
-      // the stored dxi/dx carries sqrt(W): unscale it with the geometry's weight
-      W = (T)geo[tile * NGEO * NQ + tq];
-      const T rsw = T(1) / (T)sqrt((double)W);
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) A[k][j] *= rsw;
-      // tau = 2 mu e + c I and c = lambda log J
-#pragma unroll
-      for (int m = 0; m < 6; ++m) twoe[m] = (tau[m] - (m < 3 ? c : T(0))) / mu;
-      logJ = (double)c / (double)lam;
-    } else {
-      T Gu[3][3], D[3][3];
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) Gu[i][k] = G[NC - 3 + i][k];
-      const double *g = geo + tile * NGEO * NQ + tq;
-      W = (T)g[0];
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int J = 0; J < 3; ++J) D[k][J] = (T)g[(1 + k * 3 + J) * NQ];
-      Kin<T> k;
-      kinematics(Gu, D, mu, lam, k);
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) A[i][j] = k.A[i][j];
-#pragma unroll
-      for (int m = 0; m < 6; ++m) tau[m] = k.tau[m];
-      c = k.c;
-      logJ = k.logJ;
-      for (int i = 0; i < 3; ++i)
-        for (int j = i; j < 3; ++j)
-          twoe[sym_index(i, j)] = k.H[i][j] + k.H[j][i] +
-                                  k.H[i][0] * k.H[j][0] + k.H[i][1] * k.H[j][1] + k.H[i][2] * k.H[j][2];
-    }
-    T f[3][3], M[3][3];
-    adjoint_qf(C, A, tau, c, W, mu, lam, f, M);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) a[(i * 3 + k) * Q3 + q] = f[i][k];
-    T d = 0;
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) d += M[i][j] * twoe[sym_index(i, j)];
-    pm = W * d;
-    pl = W * (T)logJ * (M[0][0] + M[1][1] + M[2][2]);
-  }
-  __syncthreads();
-  // per-element parameter gradients: stage the point values in b, sum serially
-  if (live) {
-    b[q] = pm;
-    b[Q3 + q] = pl;
-  }
-  grad_t_q<T, Q>(a, sD, q, b + 2 * Q3, live);
-  __syncthreads();
-  if (live && q == 0) {
-    T sm = 0, sl = 0;
-    for (int i = 0; i < Q3; ++i) {
-      sm += b[i];
-      sl += b[Q3 + i];
-    }
-    if (mub) mub[e] = (double)sm;
-    if (lamb) lamb[e] = (double)sl;
-  }
-  // move the transposed-gradient result to the front of b for interp_t
-  T tmp[3];
-  if (live) {
-#pragma unroll
-    for (int c2 = 0; c2 < 3; ++c2) tmp[c2] = b[2 * Q3 + c2 * Q3 + q];
-  }
-  __syncthreads();
-  if (live) {
-#pragma unroll
-    for (int c2 = 0; c2 < 3; ++c2) b[c2 * Q3 + q] = tmp[c2];
-  }
-  __syncthreads();
-  interp_t<T, P, Q, 3>(b, a, sB, q, live);
-  if (live && q < P3) store_record(ev, e, a, q, P3);
-}
-
 // Geometric factors out of the tiled layout into [E][10][Q^3].
 template <int Q>
 __global__ void k_export_geo(const double *__restrict__ geo, double *__restrict__ out, int64_t E) {
@@ -1695,16 +1664,18 @@ __global__ __launch_bounds__(256) void k_assemble_dot(int64_t N, const int32_t *
 
 inline unsigned grid1d(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-// y = assembled element records of `op`; constrained components take src (or `fill`).
+// y = assembled element records of `op`; constrained components take src (or `fill`)
+// unless they are to be kept (masked = false).
 template <typename T>
-hipError_t assemble(const hpmg_op_s &op, const T *src, T *y, hipStream_t s, T fill = T(0)) {
+hipError_t assemble(const hpmg_op_s &op, const T *src, T *y, hipStream_t s, T fill = T(0), bool masked = true) {
+  const uint8_t *mask = masked ? op.mask : nullptr;
   int64_t g = (op.N + 255) / 256;
   if (g < 1) g = 1;
   if (sweep_records<T>(op.P))
-    k_assemble_staged<T><<<(unsigned)g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, (const T *)op.evec, op.mask, src,
+    k_assemble_staged<T><<<(unsigned)g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, (const T *)op.evec, mask, src,
                                                       fill, y);
   else
-    k_assemble<T><<<(unsigned)g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, (const T *)op.evec, op.mask, src, fill,
+    k_assemble<T><<<(unsigned)g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, (const T *)op.evec, mask, src, fill,
                                                y);
   return hipGetLastError();
 }
@@ -1770,7 +1741,8 @@ hipError_t launch_residual(const hpmg_op_s &op, const double *u, double *r, bool
     lines_launch<double, p, q, 4>((unsigned)op.tiles, s, keep_records<double>(op.E, p), op.emap, u,            \
                                   (const double *)nullptr, op.geo, (const double *)nullptr, op.tab64, op.mu,      \
                                   op.lam, op.mu_e, op.lam_e, (double *)op.evec, op.E, (const double *)nullptr,    \
-                                  store ? op.state64 : nullptr, op.flags, (const double *)nullptr);               \
+                                  store ? op.state64 : nullptr, op.flags, (const double *)nullptr,                \
+                                  (double *)nullptr, (double *)nullptr);                                          \
     hipError_t e = hipGetLastError();                                                            \
     if (e != hipSuccess) return e;                                                               \
     return assemble<double>(op, nullptr, r, s);                                                  \
@@ -1791,23 +1763,23 @@ static hipError_t jacobian_pq(const hpmg_op_s &op, const hpmg_op_s &f, int mode,
     if (mode == HPMG_INITIAL_NATIVE || mode == HPMG_INITIAL_TUNED || mode == HPMG_CURRENT_20) {
       if (mode == HPMG_INITIAL_NATIVE)
         lines_launch<T, P, Q, 1>(g, s, keep, op.emap, du, nullptr, op.geo, op.sinit, tab, op.mu, op.lam, op.mu_e,
-                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr);
+                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
       else if (mode == HPMG_INITIAL_TUNED)
         lines_launch<T, P, Q, 2>(g, s, keep, op.emap, du, nullptr, op.geo, op.sinit, tab, op.mu, op.lam, op.mu_e,
-                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr);
+                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
       else
         lines_launch<T, P, Q, 3>(g, s, keep, op.emap, du, nullptr, op.geo, op.sinit, tab, op.mu, op.lam, op.mu_e,
-                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr);
+                                 op.lam_e, ev, op.E, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
       return hipGetLastError();
     }
   }
   if (mode == HPMG_STORED) {
     lines_launch<T, P, Q, 0>(g, s, keep, op.emap, du, state, nullptr, nullptr, tab, f.mu, f.lam, f.mu_e, f.lam_e,
-                             ev, op.E, stop, nullptr, nullptr, nullptr);
+                             ev, op.E, stop, nullptr, nullptr, nullptr, nullptr, nullptr);
   } else {
     lines_launch<T, P, Q, 5>(g, s, keep, op.emap, du, (const T *)nullptr, op.geo, (const double *)nullptr, tab,
                              op.mu, op.lam, op.mu_e, op.lam_e, ev, op.E, (const double *)nullptr,
-                             (double *)nullptr, (unsigned *)nullptr, u);
+                             (double *)nullptr, (unsigned *)nullptr, u, (double *)nullptr, (double *)nullptr);
   }
   return hipGetLastError();
 }
@@ -1858,29 +1830,35 @@ hipError_t launch_jacobian(const hpmg_op_s &op, int prec, int mode, const double
   return jacobian_t<float>(op, mode, u, (const float *)du, (float *)y, s);
 }
 
+template <typename T, int P, int Q>
+static void diagonal_launch(const hpmg_op_s &op, const hpmg_op_s &f, const T *state, const T *tab, hipStream_t s) {
+  const unsigned g = (unsigned)op.tiles;
+  T *ev = (T *)op.evec;
+  if constexpr (sweep_records<T>(P)) {
+    if (keep_records<T>(op.E, P))
+      k_diagonal<T, P, Q, 1><<<g, QT<Q>::NT, 0, s>>>(state, tab, f.mu, f.lam, f.mu_e, f.lam_e, ev, op.E);
+    else
+      k_diagonal<T, P, Q, 2><<<g, QT<Q>::NT, 0, s>>>(state, tab, f.mu, f.lam, f.mu_e, f.lam_e, ev, op.E);
+  } else {
+    k_diagonal<T, P, Q, 0><<<g, QT<Q>::NT, 0, s>>>(state, tab, f.mu, f.lam, f.mu_e, f.lam_e, ev, op.E);
+  }
+}
+
 hipError_t launch_diagonal(const hpmg_op_s &op, int prec, void *diag, hipStream_t s) {
   const hpmg_op_s &f = op.fine ? *op.fine : op;
-  if (prec == HPMG_F64) {
-#define X(p, q)                                                                                    \
-  if (op.P == p && op.Q == q) {                                                                    \
-    k_diagonal<double, p, q><<<(unsigned)op.tiles, QT<q>::NT, 0, s>>>(                              \
-        op.emap, f.state64, op.tab64, f.mu, f.lam, f.mu_e, f.lam_e, (double *)op.evec, op.E);    \
-    hipError_t e = hipGetLastError();                                                              \
-    return e != hipSuccess ? e : assemble<double>(op, nullptr, (double *)diag, s, 1.0);            \
+#define X(p, q)                                                                 \
+  if (op.P == p && op.Q == q) {                                                 \
+    if (prec == HPMG_F64)                                                       \
+      diagonal_launch<double, p, q>(op, f, f.state64, op.tab64, s);             \
+    else                                                                        \
+      diagonal_launch<float, p, q>(op, f, f.state32, op.tab32, s);              \
+    hipError_t e = hipGetLastError();                                           \
+    if (e != hipSuccess) return e;                                              \
+    return prec == HPMG_F64 ? assemble<double>(op, nullptr, (double *)diag, s, 1.0) \
+                            : assemble<float>(op, nullptr, (float *)diag, s, 1.0f); \
   }
-    HPMG_PQ_LIST(X)
+  HPMG_PQ_LIST(X)
 #undef X
-  } else {
-#define X(p, q)                                                                                   \
-  if (op.P == p && op.Q == q) {                                                                   \
-    k_diagonal<float, p, q><<<(unsigned)op.tiles, QT<q>::NT, 0, s>>>(                              \
-        op.emap, f.state32, op.tab32, f.mu, f.lam, f.mu_e, f.lam_e, (float *)op.evec, op.E);     \
-    hipError_t e = hipGetLastError();                                                             \
-    return e != hipSuccess ? e : assemble<float>(op, nullptr, (float *)diag, s, 1.0f);            \
-  }
-    HPMG_PQ_LIST(X)
-#undef X
-  }
   return hipErrorInvalidValue;
 }
 
@@ -1992,22 +1970,20 @@ static hipError_t vjp_t(const hpmg_op_s &op, int mode, const double *u, const T 
   T *ev = (T *)op.evec;
   const T *state = std::is_same<T, double>::value ? (const T *)op.state64 : (const T *)op.state32;
   const T *tab = std::is_same<T, double>::value ? (const T *)op.tab64 : (const T *)op.tab32;
+  const unsigned g = (unsigned)op.tiles;
 #define X(p, q)                                                                                      \
   if (op.P == p && op.Q == q) {                                                                      \
+    const bool keep = keep_records<T>(op.E, p);                                                      \
     if (mode == HPMG_STORED)                                                                         \
-      k_vjp<T, p, q, true><<<(unsigned)op.tiles, QT<q>::NT, 0, s>>>(op.emap, u, w, op.geo, state, tab,  \
-                                                                    op.mu, op.lam, op.mu_e, op.lam_e, \
-                                                                    ev, mub, lamb, op.E);            \
+      lines_launch<T, p, q, 6>(g, s, keep, op.emap, w, state, op.geo, nullptr, tab, op.mu, op.lam,   \
+                               op.mu_e, op.lam_e, ev, op.E, nullptr, nullptr, nullptr, u, mub, lamb); \
     else                                                                                             \
-      k_vjp<T, p, q, false><<<(unsigned)op.tiles, QT<q>::NT, 0, s>>>(op.emap, u, w, op.geo, state, tab, \
-                                                                     op.mu, op.lam, op.mu_e, op.lam_e, \
-                                                                     ev, mub, lamb, op.E);           \
+      lines_launch<T, p, q, 7>(g, s, keep, op.emap, w, nullptr, op.geo, nullptr, tab, op.mu, op.lam, \
+                               op.mu_e, op.lam_e, ev, op.E, nullptr, nullptr, nullptr, u, mub, lamb); \
     hipError_t e = hipGetLastError();                                                                \
     if (e != hipSuccess) return e;                                                                   \
     /* unmasked assembly: constrained columns of u_bar are kept */                                   \
-    k_assemble<T><<<grid1d(op.N, 256), 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, ev, nullptr, nullptr, \
-                                                    T(0), ub);                                       \
-    return hipGetLastError();                                                                        \
+    return assemble<T>(op, nullptr, ub, s, T(0), false);                                             \
   }
   HPMG_PQ_LIST(X)
 #undef X
