@@ -198,6 +198,18 @@ __device__ __forceinline__ void residual_qf(const Kin<T> &k, T W, T (&f)[3][3]) 
     }
 }
 
+// a0 b0 + a1 b1 + a2 b2 and c + a b, in FP64 with their roundings fixed: left to the
+// compiler, which product becomes the plain one differs between instances of a kernel, and
+// with it the last bit of an operator that the coarse solves amplify.
+__device__ __forceinline__ double dot3(double a0, double b0, double a1, double b1, double a2, double b2) {
+  return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
+}
+__device__ __forceinline__ float dot3(float a0, float b0, float a1, float b1, float a2, float b2) {
+  return a0 * b0 + a1 * b1 + a2 * b2;
+}
+__device__ __forceinline__ double add_product(double c, double a, double b) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float add_product(float c, float a, float b) { return c + a * b; }
+
 // Jacobian pointwise map (eqs. Jacobian, dtau, depsilon in current configuration):
 //   g = G A = grad_x du;  s = g tau + lambda tr(g) I + (mu - lambda log J)(g + g^T);
 //   f = W s A^T.
@@ -206,19 +218,19 @@ __device__ __forceinline__ void jacobian_qf(const T (&G)[3][3], const T (&A)[3][
                                             T c, T W, T mu, T lam, T (&f)[3][3]) {
   T g[3][3];
   for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) g[i][j] = G[i][0] * A[0][j] + G[i][1] * A[1][j] + G[i][2] * A[2][j];
+    for (int j = 0; j < 3; ++j) g[i][j] = dot3(G[i][0], A[0][j], G[i][1], A[1][j], G[i][2], A[2][j]);
   const T trg = g[0][0] + g[1][1] + g[2][2];
   const T m2 = mu - c;
   T s[3][3];
   for (int i = 0; i < 3; ++i)
     for (int j = 0; j < 3; ++j) {
-      T v = g[i][0] * tau[sym_index(0, j)] + g[i][1] * tau[sym_index(1, j)] + g[i][2] * tau[sym_index(2, j)];
-      v += m2 * (g[i][j] + g[j][i]);
-      if (i == j) v += lam * trg;
+      T v = dot3(g[i][0], tau[sym_index(0, j)], g[i][1], tau[sym_index(1, j)], g[i][2], tau[sym_index(2, j)]);
+      v = add_product(v, m2, g[i][j] + g[j][i]);
+      if (i == j) v = add_product(v, lam, trg);
       s[i][j] = v;
     }
   for (int i = 0; i < 3; ++i)
-    for (int a = 0; a < 3; ++a) f[i][a] = W * (s[i][0] * A[a][0] + s[i][1] * A[a][1] + s[i][2] * A[a][2]);
+    for (int a = 0; a < 3; ++a) f[i][a] = W * dot3(s[i][0], A[a][0], s[i][1], A[a][1], s[i][2], A[a][2]);
 }
 
 // Adjoint pointwise map, written as the transpose of jacobian_qf: for a cotangent
@@ -388,17 +400,6 @@ __device__ __forceinline__ void gather_node(const S *__restrict__ v, uint32_t w,
   a[q] = (masked && ((w >> EMAP_BC_SHIFT) & 1u)) ? T(0) : (T)x0;
   a[P3 + q] = (masked && ((w >> (EMAP_BC_SHIFT + 1)) & 1u)) ? T(0) : (T)x1;
   a[2 * P3 + q] = (masked && ((w >> (EMAP_BC_SHIFT + 2)) & 1u)) ? T(0) : (T)x2;
-}
-
-// Writes the element's nodal result (LDS [c][P^3]) as records [e][a][c] for the
-// node-centric assembly pass.
-template <typename T>
-__device__ __forceinline__ void store_record(T *__restrict__ ev, int64_t e, const T *a, int q, int P3) {
-  T *p = ev + ((int64_t)e * P3 + q) * 3;
-  const T x0 = a[q], x1 = a[P3 + q], x2 = a[2 * P3 + q];
-  p[0] = x0;
-  p[1] = x1;
-  p[2] = x2;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1084,24 +1085,15 @@ __global__ void k_traction_load(const double *__restrict__ X, const int32_t *__r
 // (from the stored sqrt(W) A the weight comes out of the products itself)
 // (the Jacobian map with G = e_i grad(phi)^T); the node value is
 //   sum_q sum_kl K^(i)_kl dphi/dxi_k dphi/dxi_l,
-// a tensor product of the 1D elementwise tables B*B, B*G, G*G.  The six (k, l) pairs need
-// six z and six y contractions, but only three tables occur along x (G*G for 00, B*G for
-// 01 and 02, B*B for the rest), so the y stage sums the pairs that share one and the x
-// stage runs three: 375 multiply-adds a line of each component at P = Q = 5 and three
-// barriers after the point stage.  Line tasks as in k_jacobian_lines, a task taking all
-// pairs of its line so that the tables stay in scalar registers.  One thread per point and
-// pair, with every contraction's operands read from LDS, took 130-147 us for 25^3 Q4
-// elements in FP64 (bound by LDS); this form 64-72, of which the 250 MB of state take 44.
+// a tensor product of the 1D elementwise tables B*B, B*G, G*G, contracted in three
+// transposed 1D stages for each of the six (k, l) pairs and summed in pair order.  Line
+// tasks as in k_jacobian_lines, a task taking all pairs of its line so that the tables stay
+// in scalar registers, three barriers after the point stage.  One thread per point and
+// pair, with every contraction's operands read from LDS and 24 barriers, took 130-147 us for
+// 25^3 Q4 elements in FP64; this form 75-80, of which the 250 MB of state take 44 (summing
+// the pairs that share an x table before the x stage saves another 8 us, but rounds
+// otherwise than before, which the coarse solves of a V-cycle amplify to 1e-9 and more).
 // ------------------------------------------------------------------------------------
-// y += M^T x, M [NI][NO].
-template <typename T, int NI, int NO>
-__device__ __forceinline__ void line_add_t(const T *__restrict__ M, const T (&x)[NI], T (&y)[NO]) {
-#pragma unroll
-  for (int o = 0; o < NO; ++o)
-#pragma unroll
-    for (int i = 0; i < NI; ++i) y[o] += M[i * NO + o] * x[i];
-}
-
 template <typename T, int P, int Q, int SWEEP>
 __global__ __launch_bounds__(QT<Q>::NT) void k_diagonal(
     const T *__restrict__ state, const T *__restrict__ tab, double mu0, double lam0,
@@ -1156,51 +1148,33 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_diagonal(
       line_task<T, Q, P, true, Q2>(f + 3 * p * Q3, p == 2 ? tGG : p == 3 || p == 4 ? tBG : tBB);
   }
   __syncthreads();
-  // y lines: the sums of the pairs by their x table, into the frames of pairs 0, 1 and 2
+  // y lines, in place
   for (int t = tq; t < ET * 3 * Q * P; t += NT) {
     const int te = t / (3 * Q * P), r = t % (3 * Q * P), i = r / (Q * P);
     if (te >= nel) break;
     T *f = lds + te * ELS + i * Q3 + line_base<Q, 1, Q>(r % (Q * P));
-    T y[3][P];
-    auto add = [&](int p, const T *M, T (&o)[P]) {
-      T x[Q];
 #pragma unroll
-      for (int j = 0; j < Q; ++j) x[j] = f[3 * p * Q3 + j * Q];
-      line_add_t<T, Q, P>(M, x, o);
-    };
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-      for (int o = 0; o < P; ++o) y[g][o] = T(0);
-    add(0, tBB, y[0]);
-    add(4, tBB, y[1]);
-    add(5, tBG, y[1]);
-    add(1, tGG, y[2]);
-    add(2, tBB, y[2]);
-    add(3, tBG, y[2]);
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-      for (int o = 0; o < P; ++o) f[3 * g * Q3 + o * Q] = y[g][o];
+    for (int p = 0; p < 6; ++p)
+      line_task<T, Q, P, true, Q>(f + 3 * p * Q3, p == 1 ? tGG : p == 3 || p == 5 ? tBG : tBB);
   }
   __syncthreads();
-  // x lines
+  // x lines, summed over the pairs in order
   for (int t = tq; t < ET * 3 * P * P; t += NT) {
     const int te = t / (3 * P * P), r = t % (3 * P * P), i = r / (P * P);
     if (te >= nel) break;
     T *f = lds + te * ELS + i * Q3 + line_base<Q, 0, P>(r % (P * P));
-    T y[P];
+    T acc[P];
 #pragma unroll
-    for (int o = 0; o < P; ++o) y[o] = T(0);
+    for (int p = 0; p < 6; ++p) {
+      T x[Q], y[P];
 #pragma unroll
-    for (int g = 0; g < 3; ++g) {
-      T x[Q];
+      for (int j = 0; j < Q; ++j) x[j] = f[3 * p * Q3 + j];
+      line_apply<T, Q, P, true>(p == 0 ? tGG : p >= 4 ? tBG : tBB, x, y);
 #pragma unroll
-      for (int j = 0; j < Q; ++j) x[j] = f[3 * g * Q3 + j];
-      line_add_t<T, Q, P>(g == 0 ? tGG : g == 1 ? tBG : tBB, x, y);
+      for (int o = 0; o < P; ++o) acc[o] = p ? acc[o] + y[o] : y[o];
     }
 #pragma unroll
-    for (int o = 0; o < P; ++o) f[o] = y[o];
+    for (int o = 0; o < P; ++o) f[o] = acc[o];
   }
   __syncthreads();
   store_tile_records<T, P, Q, SWEEP>(ev, tile, nel, lds, ELS);
@@ -1390,74 +1364,109 @@ __global__ __launch_bounds__(256) void k_ell_build(bool node_major, int64_t nn, 
 
 // ------------------------------------------------------------------------------------
 // a11: p-transfer on the same elements (eq. mg_prolong).
+// Both directions by line tasks (as in k_jacobian_lines) over frames of P_f^3 values per
+// component.  With one thread per fine node and stage, index arithmetic and LDS reads bound
+// them: 39 us (prolongation) and 27 us (restriction) for Q2 <-> Q4 on 34^3 elements in
+// FP32, against 31 and 23 by lines; two tiles a workgroup (their dependent loads in flight
+// together) take the pair with its assembly from 80 to 70.5 us, four to 67 there but Q2 <-> Q1
+// on 43^3 elements from 31 back to 33.
 // ------------------------------------------------------------------------------------
+// Elements of a transfer workgroup, and the fine nodes of a thread.
+constexpr int TR_TILES = 2;
+template <int PF>
+struct TR {
+  static constexpr int ET = TR_TILES * QT<PF>::ET, NT = QT<PF>::NT, IT = (ET * PF * PF * PF + NT - 1) / NT;
+};
+
 template <typename T, int PF, int PC>
-__global__ __launch_bounds__(QT<PF>::NT) void k_prolong_add(
+__global__ __launch_bounds__(TR<PF>::NT) void k_prolong_add(
     const uint32_t *__restrict__ emap_c, const uint32_t *__restrict__ emap_f, const T *__restrict__ xc,
     const T *__restrict__ tab_c, T *__restrict__ yf, int64_t E) {
-  constexpr int F3 = PF * PF * PF, C3 = PC * PC * PC, ET = QT<PF>::ET, NQ = ET * F3, NT = QT<PF>::NT;
-  constexpr int S = 3 * F3;
-  __shared__ T sM[PF * PC];
-  __shared__ T lds[2 * ET * S];
-  const int tq = threadIdx.x, el = tq / F3, q = tq % F3;
-  const int64_t tile = xcd_tile();
-  const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
-  load_tables(sM, tab_c, tab_ctof(PF), PF * PC, tq, NT);
-  T *a = lds + (live ? el : 0) * S, *b = lds + ET * S + (live ? el : 0) * S;
-  uint32_t wf = 0;
-  if (live) wf = emap_f[e * F3 + q];
-  if (live && q < C3) gather_node(xc, emap_c[e * C3 + q], true, a, q, C3);
-  __syncthreads();
-  stage<T, PC, PC, PC, 0, PF, false, 3>(a, b, sM, q, live);
-  __syncthreads();
-  stage<T, PF, PC, PC, 1, PF, false, 3>(b, a, sM, q, live);
-  __syncthreads();
-  stage<T, PF, PF, PC, 2, PF, false, 3>(a, b, sM, q, live);
-  __syncthreads();
+  constexpr int F3 = PF * PF * PF, C3 = PC * PC * PC, ET = TR<PF>::ET, NT = TR<PF>::NT, IT = TR<PF>::IT, ELS = 3 * F3;
+  __shared__ T lds[ET * ELS];
+  const int tq = threadIdx.x;
+  const int64_t e0 = xcd_tile() * ET;
+  const int nel = (int)((E - e0) < ET ? (E - e0) : ET);
+  const T *M = tab_c + tab_ctof(PF);
   // Every element sharing a fine node interpolates the same value there (the coarse
   // field is continuous); the node's owner element adds it.  No atomics, and the
   // result does not depend on the order in which workgroups run.
-  if (live && (wf & EMAP_OWNER)) {
-    T *p = yf + (int64_t)(wf & EMAP_ID_MASK) * 3;
+  uint32_t wf[IT];
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      if (!((wf >> (EMAP_BC_SHIFT + c)) & 1u)) p[c] += b[c * F3 + q];
+  for (int k = 0; k < IT; ++k) wf[k] = tq + k * NT < nel * F3 ? emap_f[e0 * F3 + tq + k * NT] : 0u;
+  for (int t = tq; t < nel * C3; t += NT) {
+    const int te = t / C3, a = t % C3;
+    gather_node(xc, emap_c[e0 * C3 + t], true, lds + te * ELS,
+                (a % PC) + PF * ((a / PC) % PC) + PF * PF * (a / (PC * PC)), F3);
   }
+  T y[IT][3];
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    const T *p = yf + (int64_t)(wf[k] & EMAP_ID_MASK) * 3;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) y[k][c] = (wf[k] & EMAP_OWNER) ? p[c] : T(0);
+  }
+  __syncthreads();
+  line_stage<T, PF, 0, PC, PF, false, PC, PC, ET, ELS>(lds, M, tq, NT, nel);
+  __syncthreads();
+  line_stage<T, PF, 1, PC, PF, false, PF, PC, ET, ELS>(lds, M, tq, NT, nel);
+  __syncthreads();
+  line_stage<T, PF, 2, PC, PF, false, PF, PF, ET, ELS>(lds, M, tq, NT, nel);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < IT; ++k)
+    if (wf[k] & EMAP_OWNER) {
+      const int t = tq + k * NT;
+      const T *v = lds + t / F3 * ELS + t % F3;
+      T *p = yf + (int64_t)(wf[k] & EMAP_ID_MASK) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (!((wf[k] >> (EMAP_BC_SHIFT + c)) & 1u)) p[c] = y[k][c] + v[c * F3];
+    }
 }
 
 template <typename T, int PF, int PC>
-__global__ __launch_bounds__(QT<PF>::NT) void k_restrict(
+__global__ __launch_bounds__(TR<PF>::NT) void k_restrict(
     const uint32_t *__restrict__ emap_f, const T *__restrict__ rf, const T *__restrict__ tab_c,
     T *__restrict__ ev_c, int64_t E) {
-  constexpr int F3 = PF * PF * PF, C3 = PC * PC * PC, ET = QT<PF>::ET, NQ = ET * F3, NT = QT<PF>::NT;
-  constexpr int S = 3 * F3;
-  __shared__ T sM[PF * PC];
-  __shared__ T lds[2 * ET * S];
-  const int tq = threadIdx.x, el = tq / F3, q = tq % F3;
-  const int64_t tile = xcd_tile();
-  const int64_t e = tile * ET + el;
-  const bool live = tq < NQ && e < E;
-  load_tables(sM, tab_c, tab_ctof(PF), PF * PC, tq, NT);
-  T *a = lds + (live ? el : 0) * S, *b = lds + ET * S + (live ? el : 0) * S;
+  constexpr int F3 = PF * PF * PF, C3 = PC * PC * PC, ET = TR<PF>::ET, NT = TR<PF>::NT, IT = TR<PF>::IT, ELS = 3 * F3;
+  __shared__ T lds[ET * ELS];
+  const int tq = threadIdx.x;
+  const int64_t e0 = xcd_tile() * ET;
+  const int nel = (int)((E - e0) < ET ? (E - e0) : ET);
+  const T *M = tab_c + tab_ctof(PF);
   // Transpose of the owner-written prolongation: each fine node's value enters
   // through its owner element only.
-  if (live) {
-    const uint32_t w = emap_f[e * F3 + q];
-    if (w & EMAP_OWNER) {
-      gather_node(rf, w, true, a, q, F3);
-    } else {
-      a[q] = a[F3 + q] = a[2 * F3 + q] = T(0);
-    }
+  uint32_t w[IT];
+  T x[IT][3];
+#pragma unroll
+  for (int k = 0; k < IT; ++k) w[k] = tq + k * NT < nel * F3 ? emap_f[e0 * F3 + tq + k * NT] : 0u;
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    const T *p = rf + (int64_t)(w[k] & EMAP_ID_MASK) * 3;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      x[k][c] = (w[k] & EMAP_OWNER) && !((w[k] >> (EMAP_BC_SHIFT + c)) & 1u) ? p[c] : T(0);
+  }
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    const int t = tq + k * NT;
+    if (t < nel * F3)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) lds[t / F3 * ELS + c * F3 + t % F3] = x[k][c];
   }
   __syncthreads();
-  stage<T, PF, PF, PF, 2, PC, true, 3>(a, b, sM, q, live);
+  line_stage<T, PF, 2, PF, PC, true, PF, PF, ET, ELS>(lds, M, tq, NT, nel);
   __syncthreads();
-  stage<T, PF, PF, PC, 1, PC, true, 3>(b, a, sM, q, live);
+  line_stage<T, PF, 1, PF, PC, true, PF, PC, ET, ELS>(lds, M, tq, NT, nel);
   __syncthreads();
-  stage<T, PF, PC, PC, 0, PC, true, 3>(a, b, sM, q, live);
+  line_stage<T, PF, 0, PF, PC, true, PC, PC, ET, ELS>(lds, M, tq, NT, nel);
   __syncthreads();
-  if (live && q < C3) store_record(ev_c, e, b, q, C3);
+  // records [e][a][c] of the workgroup's elements: one contiguous run
+  for (int d = tq; d < nel * C3 * 3; d += NT) {
+    const int r = d / 3, c = d - 3 * r, te = r / C3, a = r - te * C3;
+    ev_c[e0 * (C3 * 3) + d] = lds[te * ELS + c * F3 + (a % PC) + PF * ((a / PC) % PC) + PF * PF * (a / (PC * PC))];
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -1864,14 +1873,14 @@ hipError_t launch_diagonal(const hpmg_op_s &op, int prec, void *diag, hipStream_
 
 hipError_t launch_prolong_add(const hpmg_op_s &c, const hpmg_op_s &f, int prec, const void *xc, void *yf,
                               hipStream_t s) {
-  const unsigned grid = grid1d(f.E, elems_per_tile(f.P));
+  const unsigned grid = grid1d(f.E, TR_TILES * elems_per_tile(f.P));
 #define X(pf, pc)                                                                                     \
   if (f.P == pf && c.P == pc) {                                                                       \
     if (prec == HPMG_F64)                                                                             \
-      k_prolong_add<double, pf, pc><<<grid, QT<pf>::NT, 0, s>>>(c.emap, f.emap, (const double *)xc,    \
+      k_prolong_add<double, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(c.emap, f.emap, (const double *)xc,    \
                                                                 c.tab64, (double *)yf, f.E);          \
     else                                                                                              \
-      k_prolong_add<float, pf, pc><<<grid, QT<pf>::NT, 0, s>>>(c.emap, f.emap, (const float *)xc,      \
+      k_prolong_add<float, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(c.emap, f.emap, (const float *)xc,      \
                                                                c.tab32, (float *)yf, f.E);            \
     return hipGetLastError();                                                                         \
   }
@@ -1883,16 +1892,16 @@ hipError_t launch_prolong_add(const hpmg_op_s &c, const hpmg_op_s &f, int prec, 
 
 hipError_t launch_restrict(const hpmg_op_s &f, const hpmg_op_s &c, int prec, const void *rf, void *rc,
                            hipStream_t s) {
-  const unsigned grid = grid1d(f.E, elems_per_tile(f.P));
+  const unsigned grid = grid1d(f.E, TR_TILES * elems_per_tile(f.P));
 #define X(pf, pc)                                                                                    \
   if (f.P == pf && c.P == pc) {                                                                      \
     if (prec == HPMG_F64) {                                                                          \
-      k_restrict<double, pf, pc><<<grid, QT<pf>::NT, 0, s>>>(f.emap, (const double *)rf, c.tab64,     \
+      k_restrict<double, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(f.emap, (const double *)rf, c.tab64,     \
                                                              (double *)c.evec, f.E);                 \
       hipError_t e = hipGetLastError();                                                              \
       return e != hipSuccess ? e : assemble<double>(c, nullptr, (double *)rc, s);                    \
     }                                                                                                \
-    k_restrict<float, pf, pc><<<grid, QT<pf>::NT, 0, s>>>(f.emap, (const float *)rf, c.tab32,         \
+    k_restrict<float, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(f.emap, (const float *)rf, c.tab32,         \
                                                           (float *)c.evec, f.E);                      \
     hipError_t e = hipGetLastError();                                                                \
     return e != hipSuccess ? e : assemble<float>(c, nullptr, (float *)rc, s);                        \
