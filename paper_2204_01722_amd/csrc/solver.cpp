@@ -425,24 +425,30 @@ int build_ell_structure(hpmg_mg_s *mg) {
   const int64_t nn = C.N, nrec = C.E * 8;
   std::vector<int32_t> en(nrec);
   HPMG_HIP(hipMemcpy(en.data(), C.elem_nodes, nrec * sizeof(int32_t), hipMemcpyDeviceToHost));
-  std::vector<int32_t> nb((size_t)nn * ELL_MAX_W), cnt(nn, 0);
-  for (int64_t e = 0; e < C.E; ++e)
-    for (int a = 0; a < 8; ++a) {
-      const int32_t n = en[e * 8 + a];
-      if (n < 0 || n >= nn) return fail(HPMG_ERR_SHAPE, "mg_create: bad node id in the coarsest level");
-      int32_t *row = nb.data() + (size_t)n * ELL_MAX_W;
-      for (int b = 0; b < 8; ++b) {
-        const int32_t c = en[e * 8 + b];
-        bool seen = false;
-        for (int k = 0; k < cnt[n] && !seen; ++k) seen = row[k] == c;
-        if (seen) continue;
-        if (cnt[n] == ELL_MAX_W) return HPMG_OK;  // too wide: stay matrix-free
-        row[cnt[n]++] = c;
-      }
-    }
+  // records of every node, then each node's columns over its elements; seen[c] = n marks a
+  // column already taken for row n
+  std::vector<int32_t> first(nn + 1, 0), rec(nrec), cnt(nn, 0), seen(nn, -1);
+  for (int64_t k = 0; k < nrec; ++k) {
+    if (en[k] < 0 || en[k] >= nn) return fail(HPMG_ERR_SHAPE, "mg_create: bad node id in the coarsest level");
+    first[en[k] + 1]++;
+  }
+  for (int64_t n = 0; n < nn; ++n) first[n + 1] += first[n];
+  std::vector<int32_t> at(first.begin(), first.end() - 1);
+  for (int64_t k = 0; k < nrec; ++k) rec[at[en[k]]++] = (int32_t)k;
+  std::vector<int32_t> nb((size_t)nn * ELL_MAX_W);
   int w = 0;
   for (int64_t n = 0; n < nn; ++n) {
-    std::sort(nb.begin() + n * ELL_MAX_W, nb.begin() + n * ELL_MAX_W + cnt[n]);
+    int32_t *row = nb.data() + (size_t)n * ELL_MAX_W;
+    for (int32_t i = first[n]; i < first[n + 1]; ++i) {
+      const int32_t *e = en.data() + rec[i] / 8 * 8;
+      for (int b = 0; b < 8; ++b) {
+        if (seen[e[b]] == n) continue;
+        if (cnt[n] == ELL_MAX_W) return HPMG_OK;  // too wide: stay matrix-free
+        seen[e[b]] = (int32_t)n;
+        row[cnt[n]++] = e[b];
+      }
+    }
+    std::sort(row, row + cnt[n]);
     w = std::max(w, cnt[n]);
   }
   // padding slots hold -1 - n: the node itself, with a zero block
