@@ -135,6 +135,17 @@ hipError_t launch_mark_owners(const hpmg_op_s &op, hipStream_t s);
 // (ceil(N / 256) of them, in pq).  With `stop` set, every kernel of the apply returns at once while *stop != 0.
 hipError_t launch_jacobian_dot(const hpmg_op_s &op, int prec, const void *du, void *y, double *pq,
                                const double *stop, hipStream_t s);
+// Stored-mode apply to a smoother's vector, its assembly finished as a Chebyshev step, the
+// first step from a nonzero x, or the residual (k_assemble_smooth); c1, c2: the step's
+// factors, c1 = 1 / theta for the first.
+enum { SMOOTH_STEP, SMOOTH_FIRST, SMOOTH_RESIDUAL };
+struct Smooth {
+  int kind;
+  const void *dinv, *b;
+  void *r, *d, *x;
+  double c1, c2;
+};
+hipError_t launch_jacobian_smooth(const hpmg_op_s &op, int prec, const Smooth &sm, hipStream_t s);
 // Fused Jacobi-PCG iteration on the slots above; all kernels return at once while
 // sc[SC_STOP] != 0.  update2 records alpha in *alpha_rec, dir2 beta in *beta_rec (when
 // not null), counts the iteration in sc[SC_COUNT] and sets the stop flag on breakdown
@@ -239,10 +250,8 @@ hipError_t launch_dot_pair(int prec, int64_t n, const void *z, const void *a, co
                            double *partial, double *out, hipStream_t s);  // out = {z.a, z.b}
 hipError_t launch_cast(int64_t n, int to_prec, const void *x, void *y, hipStream_t s);
 hipError_t launch_recip(int prec, int64_t n, void *x, hipStream_t s);
-hipError_t launch_cheb_first(int prec, int64_t n, const void *dinv, const void *b, const void *Ax,
-                             void *r, void *d, void *x, double inv_theta, hipStream_t s);
-hipError_t launch_cheb_step(int prec, int64_t n, const void *dinv, void *r, const void *Ad, void *d,
-                            void *x, double c1, double c2, hipStream_t s);
+hipError_t launch_cheb_first(int prec, int64_t n, const void *dinv, const void *b, void *r, void *d, void *x,
+                             double inv_theta, hipStream_t s);  // from x = 0
 
 
 size_t prec_size(int prec);

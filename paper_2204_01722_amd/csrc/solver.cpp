@@ -144,13 +144,6 @@ int read_scalars(hpmg_mg_s *mg, int count, hipStream_t s) {
   return HPMG_OK;
 }
 
-int apply(hpmg_mg_s *mg, const Level &L, int prec, const void *in, void *out, hipStream_t s) {
-  HPMG_HIP(launch_jacobian(*L.op, prec, HPMG_STORED, nullptr, in, out, s));
-  const size_t l = &L - mg->lv.data();
-  if (l < 8) mg->n_applies[l]++;
-  return HPMG_OK;
-}
-
 // Largest eigenvalue of a symmetric tridiagonal matrix by Sturm-sequence bisection.
 double tridiag_max_eig(const std::vector<double> &a, const std::vector<double> &b) {
   const int k = (int)a.size();
@@ -349,6 +342,23 @@ int pcg_device(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, int fi
   return HPMG_OK;
 }
 
+// A L.x or A L.d, used at once as the smoother's step or residual (b - A x into L.r).
+int smooth(hpmg_mg_s *mg, Level &L, int prec, int kind, double c1, double c2, hipStream_t s) {
+  Smooth sm{};
+  sm.kind = kind;
+  sm.dinv = L.dinv;
+  sm.b = L.b;
+  sm.r = L.r;
+  sm.d = L.d;
+  sm.x = L.x;
+  sm.c1 = c1;
+  sm.c2 = c2;
+  HPMG_HIP(launch_jacobian_smooth(*L.op, prec, sm, s));
+  const size_t l = &L - mg->lv.data();
+  if (l < 8) mg->n_applies[l]++;
+  return HPMG_OK;
+}
+
 // Chebyshev semi-iteration for D^{-1}A on [lo, hi] * lambda_max, `degree` updates of
 // L.x (Ax of the initial guess skipped when it is zero).
 int chebyshev(hpmg_mg_s *mg, Level &L, int prec, bool x_zero, hipStream_t s) {
@@ -357,16 +367,13 @@ int chebyshev(hpmg_mg_s *mg, Level &L, int prec, bool x_zero, hipStream_t s) {
   const double theta = 0.5 * (bb + a), delta = 0.5 * (bb - a);
   const double sigma = theta / delta;
   double rho = 1.0 / sigma;
-  if (x_zero) {
-    HPMG_HIP(launch_cheb_first(prec, L.n, L.dinv, L.b, nullptr, L.r, L.d, L.x, 1.0 / theta, s));
-  } else {
-    if ((st = apply(mg, L, prec, L.x, L.t, s))) return st;
-    HPMG_HIP(launch_cheb_first(prec, L.n, L.dinv, L.b, L.t, L.r, L.d, L.x, 1.0 / theta, s));
-  }
+  if (x_zero)
+    HPMG_HIP(launch_cheb_first(prec, L.n, L.dinv, L.b, L.r, L.d, L.x, 1.0 / theta, s));
+  else if ((st = smooth(mg, L, prec, SMOOTH_FIRST, 1.0 / theta, 0.0, s)))
+    return st;
   for (int k = 1; k < mg->prm.cheb_degree; ++k) {
-    if ((st = apply(mg, L, prec, L.d, L.t, s))) return st;
     const double rho_new = 1.0 / (2.0 * sigma - rho);
-    HPMG_HIP(launch_cheb_step(prec, L.n, L.dinv, L.r, L.t, L.d, L.x, rho_new * rho, 2.0 * rho_new / delta, s));
+    if ((st = smooth(mg, L, prec, SMOOTH_STEP, rho_new * rho, 2.0 * rho_new / delta, s))) return st;
     rho = rho_new;
   }
   return HPMG_OK;
@@ -391,8 +398,7 @@ int cycle(hpmg_mg_s *mg, int l, hipStream_t s) {
   }
   Level &C = mg->lv[l + 1];
   if ((st = chebyshev(mg, L, prec, true, s))) return st;
-  if ((st = apply(mg, L, prec, L.x, L.t, s))) return st;
-  HPMG_HIP(launch_waxpby(prec, L.n, 1.0, L.b, -1.0, L.t, L.r, s));
+  if ((st = smooth(mg, L, prec, SMOOTH_RESIDUAL, 0.0, 0.0, s))) return st;
   HPMG_HIP(launch_restrict(*L.op, *C.op, prec, L.r, C.b, s));
   if ((st = cycle(mg, l + 1, s))) return st;
   HPMG_HIP(launch_prolong_add(*C.op, *L.op, prec, C.x, L.x, s));
@@ -404,6 +410,16 @@ int vcycle(hpmg_mg_s *mg, const double *r, double *z, hipStream_t s) {
   mg->n_vcycles++;
   Level &L = mg->lv[0];
   const int prec = prec_of(mg);
+  if (prec == HPMG_F64 && (r + L.n <= z || z + L.n <= r)) {
+    // the fine level works on the caller's vectors: b is only read, x is the result
+    void *const b = L.b, *const x = L.x;
+    L.b = const_cast<double *>(r);
+    L.x = z;
+    st = cycle(mg, 0, s);
+    L.b = b;
+    L.x = x;
+    return st;
+  }
   if (prec == HPMG_F64)
     HPMG_HIP(launch_waxpby(HPMG_F64, L.n, 1.0, r, 0.0, r, L.b, s));
   else

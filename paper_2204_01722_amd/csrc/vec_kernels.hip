@@ -64,30 +64,16 @@ __global__ void k_recip(int64_t n, T *__restrict__ x) {
   GRID_STRIDE(i, n) { x[i] = T(1) / x[i]; }
 }
 
-// r = Dinv (b - Ax); d = r / theta; x = d (Ax == null: zero initial guess) or x += d.
+// The smoother's first step from x = 0: r = Dinv b; d = r / theta; x = d.
 template <typename T>
-__global__ void k_cheb_first(int64_t n, const T *__restrict__ dinv, const T *__restrict__ b,
-                             const T *__restrict__ Ax, T *__restrict__ r, T *__restrict__ d,
-                             T *__restrict__ x, T inv_theta) {
+__global__ void k_cheb_first(int64_t n, const T *__restrict__ dinv, const T *__restrict__ b, T *__restrict__ r,
+                             T *__restrict__ d, T *__restrict__ x, T inv_theta) {
   GRID_STRIDE(i, n) {
-    const T ri = dinv[i] * (Ax ? b[i] - Ax[i] : b[i]);
+    const T ri = dinv[i] * b[i];
     const T di = ri * inv_theta;
     r[i] = ri;
     d[i] = di;
-    x[i] = Ax ? x[i] + di : di;
-  }
-}
-
-// r -= Dinv A d; d = c1 d + c2 r; x += d.
-template <typename T>
-__global__ void k_cheb_step(int64_t n, const T *__restrict__ dinv, T *__restrict__ r,
-                            const T *__restrict__ Ad, T *__restrict__ d, T *__restrict__ x, T c1, T c2) {
-  GRID_STRIDE(i, n) {
-    const T ri = r[i] - dinv[i] * Ad[i];
-    const T di = c1 * d[i] + c2 * ri;
-    r[i] = ri;
-    d[i] = di;
-    x[i] += di;
+    x[i] = di;
   }
 }
 
@@ -1051,24 +1037,13 @@ hipError_t launch_recip(int prec, int64_t n, void *x, hipStream_t s) {
            (k_recip<float><<<grid_for(n), BS, 0, s>>>(n, (float *)x)));
 }
 
-hipError_t launch_cheb_first(int prec, int64_t n, const void *dinv, const void *b, const void *Ax, void *r,
-                             void *d, void *x, double inv_theta, hipStream_t s) {
+hipError_t launch_cheb_first(int prec, int64_t n, const void *dinv, const void *b, void *r, void *d, void *x,
+                             double inv_theta, hipStream_t s) {
   DISPATCH(prec,
-           (k_cheb_first<double><<<grid_for(n), BS, 0, s>>>(n, (const double *)dinv, (const double *)b,
-                                                            (const double *)Ax, (double *)r, (double *)d,
-                                                            (double *)x, inv_theta)),
-           (k_cheb_first<float><<<grid_for(n), BS, 0, s>>>(n, (const float *)dinv, (const float *)b,
-                                                           (const float *)Ax, (float *)r, (float *)d,
-                                                           (float *)x, (float)inv_theta)));
-}
-
-hipError_t launch_cheb_step(int prec, int64_t n, const void *dinv, void *r, const void *Ad, void *d, void *x,
-                            double c1, double c2, hipStream_t s) {
-  DISPATCH(prec,
-           (k_cheb_step<double><<<grid_for(n), BS, 0, s>>>(n, (const double *)dinv, (double *)r,
-                                                           (const double *)Ad, (double *)d, (double *)x, c1, c2)),
-           (k_cheb_step<float><<<grid_for(n), BS, 0, s>>>(n, (const float *)dinv, (float *)r, (const float *)Ad,
-                                                          (float *)d, (float *)x, (float)c1, (float)c2)));
+           (k_cheb_first<double><<<grid_for(n), BS, 0, s>>>(n, (const double *)dinv, (const double *)b, (double *)r,
+                                                            (double *)d, (double *)x, inv_theta)),
+           (k_cheb_first<float><<<grid_for(n), BS, 0, s>>>(n, (const float *)dinv, (const float *)b, (float *)r,
+                                                           (float *)d, (float *)x, (float)inv_theta)));
 }
 
 hipError_t launch_dot(int prec, int64_t n, const void *x, const void *y, double *partial, double *out,
