@@ -137,7 +137,7 @@ def _p(t):
             raise ValueError("device tensor expected")
         if not t.is_contiguous():
             raise ValueError("contiguous tensor expected")
-        return C.c_void_p(t.data_ptr())
+        return t.data_ptr()
     return t
 
 
@@ -158,30 +158,35 @@ def _vec(v, n_nodes, dtype, device, what):
     return v
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# The current stream's handle on the current device.  The public accessor builds a Stream
+# object on each call (3.1 us of the 13.9 us that a small Jacobian apply took on the host).
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
+
+
+_PRECS = {F64: F64, "f64": F64, "fp64": F64, torch.float64: F64, F32: F32, "f32": F32, "fp32": F32,
+          torch.float32: F32}
+_MODES = {STORED: STORED, "stored": STORED, RECOMPUTE: RECOMPUTE, "recompute": RECOMPUTE,
+          INITIAL_NATIVE: INITIAL_NATIVE, "initial_native": INITIAL_NATIVE, INITIAL_TUNED: INITIAL_TUNED,
+          "initial_tuned": INITIAL_TUNED, CURRENT_20: CURRENT_20, "current_20": CURRENT_20}
 
 
 def _prec(p):
-    if p in (F64, "f64", "fp64", torch.float64):
-        return F64
-    if p in (F32, "f32", "fp32", torch.float32):
-        return F32
-    raise ValueError(f"bad precision {p!r}")
+    try:
+        return _PRECS[p]
+    except (KeyError, TypeError):
+        raise ValueError(f"bad precision {p!r}") from None
 
 
 def _mode(m):
-    if m in (STORED, "stored"):
-        return STORED
-    if m in (RECOMPUTE, "recompute"):
-        return RECOMPUTE
-    if m in (INITIAL_NATIVE, "initial_native"):
-        return INITIAL_NATIVE
-    if m in (INITIAL_TUNED, "initial_tuned"):
-        return INITIAL_TUNED
-    if m in (CURRENT_20, "current_20"):
-        return CURRENT_20
-    raise ValueError(f"bad mode {m!r}")
+    try:
+        return _MODES[m]
+    except (KeyError, TypeError):
+        raise ValueError(f"bad mode {m!r}") from None
 
 
 def _dtype(prec):
@@ -225,6 +230,7 @@ class Operator:
         if mask is not None and (mask.dtype != torch.uint8 or mask.numel() != 3 * n_nodes):
             raise ValueError("mask must be uint8 [n_nodes][3]")
         self.P, self.Q, self.n_nodes = P, Q, int(n_nodes)
+        self.n_dof = 3 * self.n_nodes
         self.n_elem = int(elem_nodes.shape[0])
         self.device = elem_nodes.device
         self._keep = [elem_nodes, mask]
@@ -251,10 +257,6 @@ class Operator:
             _lib.hpmg_op_destroy(h)
             self.h = None
 
-    @property
-    def n_dof(self):
-        return 3 * self.n_nodes
-
     def info(self):
         arr = (C.c_int64 * 8)()
         _check(lib().hpmg_op_info(self.h, C.cast(arr, C.c_void_p)))
@@ -276,13 +278,22 @@ class Operator:
     def _vec(self, dtype=torch.float64):
         return torch.empty(self.n_nodes, 3, dtype=dtype, device=self.device)
 
+    def _fits(self, v, dtype):
+        """Whether ``v`` is an L-vector of this operator as the library takes it."""
+        return (isinstance(v, torch.Tensor) and v.dtype is dtype and v.numel() == self.n_dof
+                and v.device == self.device and v.is_cuda and v.is_contiguous())
+
     def _in(self, v, dtype=torch.float64, what="vector"):
+        if self._fits(v, dtype):
+            return v
         if isinstance(v, torch.Tensor) and v.dtype == dtype and v.numel() == self.n_dof:
             v = v.contiguous()
         return _vec(v, self.n_nodes, dtype, self.device, what)
 
     def _out(self, out, dtype):
-        return self._vec(dtype) if out is None else _vec(out, self.n_nodes, dtype, self.device, "out")
+        if out is None:
+            return self._vec(dtype)
+        return out if self._fits(out, dtype) else _vec(out, self.n_nodes, dtype, self.device, "out")
 
     def state_version(self) -> int:
         """Counter of the stored linearisation this operator applies (bumped whenever
@@ -341,7 +352,9 @@ class Operator:
     def residual(self, u, store_state: bool = True, out=None):
         u = self._in(u, what="u")
         r = self._out(out, torch.float64)
-        _check(lib().hpmg_residual(self.h, _p(u), _p(r), int(bool(store_state)), _stream()))
+        st = _lib.hpmg_residual(self.h, u.data_ptr(), r.data_ptr(), int(bool(store_state)), _stream())
+        if st:
+            _check(st)
         return r
 
     def jacobian(self, du, precision="f64", mode="stored", u=None, out=None):
@@ -349,7 +362,10 @@ class Operator:
         du = self._in(du, _dtype(prec), "du")
         uu = None if u is None else self._in(u, what="u")
         y = self._out(out, _dtype(prec))
-        _check(lib().hpmg_jacobian_apply(self.h, prec, md, _p(uu), _p(du), _p(y), _stream()))
+        st = _lib.hpmg_jacobian_apply(self.h, prec, md, None if uu is None else uu.data_ptr(), du.data_ptr(),
+                                      y.data_ptr(), _stream())
+        if st:
+            _check(st)
         return y
 
     def state_cast_f32(self):
@@ -379,8 +395,10 @@ class Operator:
         if want_params:
             mub = torch.empty(self.n_elem, dtype=torch.float64, device=self.device)
             lamb = torch.empty(self.n_elem, dtype=torch.float64, device=self.device)
-        _check(lib().hpmg_residual_vjp(self.h, prec, _mode(mode), _p(u), _p(w), _p(ub), _p(mub), _p(lamb),
-                                       _stream()))
+        st = _lib.hpmg_residual_vjp(self.h, prec, _mode(mode), u.data_ptr(), w.data_ptr(), ub.data_ptr(), _p(mub),
+                                    _p(lamb), _stream())
+        if st:
+            _check(st)
         return ub, mub, lamb
 
 
