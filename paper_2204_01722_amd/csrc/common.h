@@ -18,8 +18,13 @@ namespace hpmg {
 // thread per quadrature point, so each field is read by one contiguous, fully coalesced
 // sweep of the workgroup.
 // ---------------------------------------------------------------------------------
+// Workgroups of 256 threads (Q = 5: of 250 points); at Q = 4 an element's 64 points are one
+// wave, whose workgroup needs no barriers: against four elements a workgroup, Q3 applies on
+// 30^3 elements in FP32 38.8 -> 37.4 us and the FP32 adjoint on 23^3 30.6 -> 29.3, FP64 alike
+// (71.4).  Measured and not better: one or three elements at Q = 5 (Q4 34^3 FP64 205.1 and
+// 215.5 against 204.3 us), half-sized workgroups at Q = 2 and 3 (within 3 % either way).
 constexpr int elems_per_tile(int Q) {
-  return Q == 2 ? 32 : Q == 3 ? 9 : Q == 4 ? 4 : Q == 5 ? 2 : 1;
+  return Q == 2 ? 32 : Q == 3 ? 9 : Q == 4 ? 1 : Q == 5 ? 2 : 1;
 }
 constexpr int tile_threads(int Q) {
   return ((elems_per_tile(Q) * Q * Q * Q + 63) / 64) * 64;

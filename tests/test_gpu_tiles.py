@@ -8,7 +8,7 @@ from _support import LAM, MU, ensure_built, gpu_available, inputs, print_case, r
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
 TOL = {"f64": 1e-12, "f32": 1e-5}  # those of the operator tests
-# elements a transfer workgroup takes: 2 x (32, 9, 4, 2) for fine orders 1..4
+# elements a transfer workgroup takes: 2 x (9, 1, 2) for fine orders 2..4
 SIZES = [(1, 1, 1), (3, 1, 1), (4, 1, 1), (5, 1, 1), (7, 1, 1), (17, 1, 1), (2, 3, 3), (19, 1, 1), (5, 3, 2)]
 
 
