@@ -142,12 +142,12 @@ hipError_t launch_jacobian_dot(const hpmg_op_s &op, int prec, const void *du, vo
                                const double *stop, hipStream_t s);
 // Stored-mode apply to a smoother's vector, its assembly finished as a Chebyshev step, the
 // first step from a nonzero x, or the residual (k_assemble_smooth); c1, c2: the step's
-// factors, c1 = 1 / theta for the first.
-enum { SMOOTH_STEP, SMOOTH_FIRST, SMOOTH_RESIDUAL };
+// factors, c1 = 1 / theta for the first.  SMOOTH_START belongs to launch_restrict.
+enum { SMOOTH_STEP, SMOOTH_FIRST, SMOOTH_RESIDUAL, SMOOTH_START };
 struct Smooth {
   int kind;
-  const void *dinv, *b;
-  void *r, *d, *x;
+  const void *dinv;
+  void *b, *r, *d, *x;
   double c1, c2;
 };
 hipError_t launch_jacobian_smooth(const hpmg_op_s &op, int prec, const Smooth &sm, hipStream_t s);
@@ -155,7 +155,9 @@ hipError_t launch_jacobian_smooth(const hpmg_op_s &op, int prec, const Smooth &s
 // sc[SC_STOP] != 0.  update2 records alpha in *alpha_rec, dir2 beta in *beta_rec (when
 // not null), counts the iteration in sc[SC_COUNT] and sets the stop flag on breakdown
 // or when r.r <= rtol2 * sc[SC_RR0] (rtol2 < 0: never).
-hipError_t launch_pcg_begin(double *sc, hipStream_t s);
+// The start from x = 0 (x null: not formed): r = b, z = D^-1 r, p = z and the scalars.
+hipError_t launch_pcg_start(int prec, int64_t n, const void *dinv, const void *b, void *x, void *r, void *z, void *p,
+                            double *partial, double *sc, hipStream_t s);
 // FCG steps on the slots above (FP64): update: alpha = r.z / p.q from the device
 // scalars (0 on a breakdown, p.q <= 0 or r.z not finite, which sets sc[FCG_BRK]),
 // x += alpha p, rn = r - alpha q, sc[FCG_RR] = rn.rn.  dir: beta = (z.rn - z.r) / r.z,
@@ -227,8 +229,10 @@ hipError_t launch_jacobian(const hpmg_op_s &op, int prec, int mode, const double
 hipError_t launch_diagonal(const hpmg_op_s &op, int prec, void *diag, hipStream_t s);
 hipError_t launch_prolong_add(const hpmg_op_s &coarse, const hpmg_op_s &fine, int prec,
                               const void *xc, void *yf, hipStream_t s);
+// start: the coarse residual goes to start->b and the smoother's first step from x = 0 is
+// made at once (rc unused).
 hipError_t launch_restrict(const hpmg_op_s &fine, const hpmg_op_s &coarse, int prec, const void *rf,
-                           void *rc, hipStream_t s);
+                           void *rc, hipStream_t s, const Smooth *start = nullptr);
 hipError_t launch_energy(const hpmg_op_s &op, const double *u, double *psi, hipStream_t s);
 hipError_t launch_vjp(const hpmg_op_s &op, int prec, int mode, const double *u, const void *w, void *ub,
                       double *mub, double *lamb, hipStream_t s);
@@ -249,8 +253,6 @@ hipError_t launch_waxpby(int prec, int64_t n, double a, const void *x, double b,
                          void *w, hipStream_t s);  // w = a x + b y
 hipError_t launch_cg_update(int prec, int64_t n, double alpha, const void *p, const void *q, void *x,
                             const void *r_in, void *r_out, hipStream_t s);  // x += a p; r_out = r_in - a q
-hipError_t launch_jacobi_dot(int prec, int64_t n, const void *dinv, const void *r, void *z,
-                             double *partial, double *out, hipStream_t s);  // z = dinv r; out = {r.z, r.r}
 hipError_t launch_dot_pair(int prec, int64_t n, const void *z, const void *a, const void *b,
                            double *partial, double *out, hipStream_t s);  // out = {z.a, z.b}
 hipError_t launch_cast(int64_t n, int to_prec, const void *x, void *y, hipStream_t s);

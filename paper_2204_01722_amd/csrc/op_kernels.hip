@@ -1653,6 +1653,8 @@ __global__ __launch_bounds__(256) void k_assemble_staged(int64_t N, const int32_
 //   SMOOTH_STEP:  in = d: r -= D^-1 A d; d = c1 d + c2 r; x += d
 //   SMOOTH_FIRST: in = x: r = D^-1 (b - A x); d = c1 r; x += d
 //   SMOOTH_RESIDUAL: in = x: r = b - A x
+//   SMOOTH_START: the sums are a restricted residual, 0 on constrained components:
+//     b = sums, r = D^-1 b; d = c1 r; x = d (the first step from x = 0)
 // The vectors are read and written in contiguous sweeps of 768 values; their loads go out
 // before the sums.
 template <typename T, int KIND>
@@ -1663,9 +1665,10 @@ __global__ __launch_bounds__(256) void k_assemble_smooth(int64_t N, const int32_
   const int64_t n0 = xcd_tile() * 256, n = n0 + threadIdx.x;
   const int nv = 3 * (int)((N - n0) < 256 ? (N - n0) : 256);
   T *r = (T *)sm.r + n0 * 3, *d = (T *)sm.d + n0 * 3, *x = (T *)sm.x + n0 * 3;
-  const T *b = (const T *)sm.b + n0 * 3, *dinv = (const T *)sm.dinv + n0 * 3;
+  T *b = (T *)sm.b + n0 * 3;
+  const T *dinv = (const T *)sm.dinv + n0 * 3;
   const T c1 = (T)sm.c1, c2 = (T)sm.c2;
-  constexpr bool STEP = KIND == SMOOTH_STEP, FIRST = KIND == SMOOTH_FIRST;
+  constexpr bool STEP = KIND == SMOOTH_STEP, START = KIND == SMOOTH_START;
   T vd[3], vx[3], vr[3], vi[3];
   bool fixed[3];
 #pragma unroll
@@ -1674,8 +1677,8 @@ __global__ __launch_bounds__(256) void k_assemble_smooth(int64_t N, const int32_
     const bool in = i < nv;
     fixed[j] = in && mask && mask[n0 * 3 + i];
     vd[j] = in && STEP ? d[i] : T(0);
-    vx[j] = in ? x[i] : T(0);
-    vr[j] = in ? (STEP ? r[i] : b[i]) : T(0);
+    vx[j] = in && !START ? x[i] : T(0);
+    vr[j] = in && !START ? (STEP ? r[i] : b[i]) : T(0);
     vi[j] = in && KIND != SMOOTH_RESIDUAL ? dinv[i] : T(0);
   }
   if (n < N) {
@@ -1689,8 +1692,14 @@ __global__ __launch_bounds__(256) void k_assemble_smooth(int64_t N, const int32_
   for (int j = 0; j < 3; ++j) {
     const int i = threadIdx.x + 256 * j;
     if (i >= nv) continue;
-    const T A = fixed[j] ? (STEP ? vd[j] : vx[j]) : buf[i];
-    if constexpr (KIND == SMOOTH_RESIDUAL) {
+    const T A = fixed[j] ? (STEP ? vd[j] : vx[j]) : buf[i];  // START: 0 where constrained
+    if constexpr (START) {
+      const T ri = vi[j] * A, di = ri * c1;
+      b[i] = A;
+      r[i] = ri;
+      d[i] = di;
+      x[i] = di;
+    } else if constexpr (KIND == SMOOTH_RESIDUAL) {
       r[i] = vr[j] - A;
     } else {
       const T ri = STEP ? fma_t(-vi[j], A, vr[j]) : vi[j] * (vr[j] - A);
@@ -1865,8 +1874,10 @@ static hipError_t assemble_smooth(const hpmg_op_s &op, const Smooth &sm, hipStre
     k_assemble_smooth<T, SMOOTH_STEP><<<g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, ev, op.mask, sm);
   else if (sm.kind == SMOOTH_FIRST)
     k_assemble_smooth<T, SMOOTH_FIRST><<<g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, ev, op.mask, sm);
-  else
+  else if (sm.kind == SMOOTH_RESIDUAL)
     k_assemble_smooth<T, SMOOTH_RESIDUAL><<<g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, ev, op.mask, sm);
+  else
+    k_assemble_smooth<T, SMOOTH_START><<<g, 256, 0, s>>>(op.N, op.csr_off, op.csr_inc, ev, op.mask, sm);
   return hipGetLastError();
 }
 
@@ -2004,22 +2015,22 @@ hipError_t launch_prolong_add(const hpmg_op_s &c, const hpmg_op_s &f, int prec, 
   return hipErrorInvalidValue;
 }
 
+template <typename T, int PF, int PC>
+static hipError_t restrict_t(const hpmg_op_s &f, const hpmg_op_s &c, const void *rf, const T *tab, void *rc,
+                             const Smooth *start, hipStream_t s) {
+  const unsigned grid = grid1d(f.E, TR<PF>::ET);
+  k_restrict<T, PF, PC><<<grid, TR<PF>::NT, 0, s>>>(f.emap, (const T *)rf, tab, (T *)c.evec, f.E);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return start ? assemble_smooth<T>(c, *start, s) : assemble<T>(c, nullptr, (T *)rc, s);
+}
+
 hipError_t launch_restrict(const hpmg_op_s &f, const hpmg_op_s &c, int prec, const void *rf, void *rc,
-                           hipStream_t s) {
-  const unsigned grid = grid1d(f.E, TR_TILES * elems_per_tile(f.P));
-#define X(pf, pc)                                                                                    \
-  if (f.P == pf && c.P == pc) {                                                                      \
-    if (prec == HPMG_F64) {                                                                          \
-      k_restrict<double, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(f.emap, (const double *)rf, c.tab64,     \
-                                                             (double *)c.evec, f.E);                 \
-      hipError_t e = hipGetLastError();                                                              \
-      return e != hipSuccess ? e : assemble<double>(c, nullptr, (double *)rc, s);                    \
-    }                                                                                                \
-    k_restrict<float, pf, pc><<<grid, TR<pf>::NT, 0, s>>>(f.emap, (const float *)rf, c.tab32,         \
-                                                          (float *)c.evec, f.E);                      \
-    hipError_t e = hipGetLastError();                                                                \
-    return e != hipSuccess ? e : assemble<float>(c, nullptr, (float *)rc, s);                        \
-  }
+                           hipStream_t s, const Smooth *start) {
+#define X(pf, pc)                                                                                \
+  if (f.P == pf && c.P == pc)                                                                    \
+    return prec == HPMG_F64 ? restrict_t<double, pf, pc>(f, c, rf, c.tab64, rc, start, s)        \
+                            : restrict_t<float, pf, pc>(f, c, rf, c.tab32, rc, start, s);
   HPMG_PP_LIST(X)
 #undef X
   return hipErrorInvalidValue;

@@ -283,11 +283,7 @@ int pcg_device(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, int fi
   double *sc = mg->scal;
   const bool record = alphas && betas;
   if (record && (fixed <= 0 || fixed > PCG_RECORD)) return fail(HPMG_ERR_ARG, "pcg: bad recording length");
-  HPMG_HIP(launch_init_bc(prec, L.n / 3, nullptr, nullptr, L.x, s));
-  HPMG_HIP(launch_waxpby(prec, L.n, 1.0, L.b, 0.0, L.b, L.r, s));
-  HPMG_HIP(launch_jacobi_dot(prec, L.n, L.dinv, L.r, L.z, mg->red, sc + 2, s));  // sc[2] = rz, sc[3] = rr
-  HPMG_HIP(launch_waxpby(prec, L.n, 1.0, L.z, 0.0, L.z, L.d, s));
-  HPMG_HIP(launch_pcg_begin(sc, s));
+  HPMG_HIP(launch_pcg_start(prec, L.n, L.dinv, L.b, record ? nullptr : L.x, L.r, L.z, L.d, mg->red, sc, s));
   const size_t l = &L - mg->lv.data();
   const int limit = fixed > 0 ? fixed : maxit;
   const double rtol2 = fixed > 0 ? -1.0 : rtol * rtol;
@@ -342,8 +338,7 @@ int pcg_device(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, int fi
   return HPMG_OK;
 }
 
-// A L.x or A L.d, used at once as the smoother's step or residual (b - A x into L.r).
-int smooth(hpmg_mg_s *mg, Level &L, int prec, int kind, double c1, double c2, hipStream_t s) {
+Smooth smoother(const Level &L, int kind, double c1, double c2) {
   Smooth sm{};
   sm.kind = kind;
   sm.dinv = L.dinv;
@@ -353,23 +348,37 @@ int smooth(hpmg_mg_s *mg, Level &L, int prec, int kind, double c1, double c2, hi
   sm.x = L.x;
   sm.c1 = c1;
   sm.c2 = c2;
+  return sm;
+}
+
+// A L.x or A L.d, used at once as the smoother's step or residual (b - A x into L.r).
+int smooth(hpmg_mg_s *mg, Level &L, int prec, int kind, double c1, double c2, hipStream_t s) {
+  const Smooth sm = smoother(L, kind, c1, c2);
   HPMG_HIP(launch_jacobian_smooth(*L.op, prec, sm, s));
   const size_t l = &L - mg->lv.data();
   if (l < 8) mg->n_applies[l]++;
   return HPMG_OK;
 }
 
-// Chebyshev semi-iteration for D^{-1}A on [lo, hi] * lambda_max, `degree` updates of
-// L.x (Ax of the initial guess skipped when it is zero).
-int chebyshev(hpmg_mg_s *mg, Level &L, int prec, bool x_zero, hipStream_t s) {
-  int st;
+// theta and delta of the Chebyshev interval on [lo, hi] * lambda_max.
+void cheb_interval(const hpmg_mg_s *mg, const Level &L, double *theta, double *delta) {
   const double a = mg->prm.cheb_lo * L.lam, bb = mg->prm.cheb_hi * L.lam;
-  const double theta = 0.5 * (bb + a), delta = 0.5 * (bb - a);
+  *theta = 0.5 * (bb + a);
+  *delta = 0.5 * (bb - a);
+}
+
+// Chebyshev semi-iteration for D^{-1}A on [lo, hi] * lambda_max, `degree` updates of
+// L.x.  The first one: made already, from x = 0 (Ax skipped), or from the given L.x.
+enum class First { done, from_zero, from_x };
+int chebyshev(hpmg_mg_s *mg, Level &L, int prec, First first, hipStream_t s) {
+  int st;
+  double theta, delta;
+  cheb_interval(mg, L, &theta, &delta);
   const double sigma = theta / delta;
   double rho = 1.0 / sigma;
-  if (x_zero)
+  if (first == First::from_zero)
     HPMG_HIP(launch_cheb_first(prec, L.n, L.dinv, L.b, L.r, L.d, L.x, 1.0 / theta, s));
-  else if ((st = smooth(mg, L, prec, SMOOTH_FIRST, 1.0 / theta, 0.0, s)))
+  else if (first == First::from_x && (st = smooth(mg, L, prec, SMOOTH_FIRST, 1.0 / theta, 0.0, s)))
     return st;
   for (int k = 1; k < mg->prm.cheb_degree; ++k) {
     const double rho_new = 1.0 / (2.0 * sigma - rho);
@@ -379,7 +388,9 @@ int chebyshev(hpmg_mg_s *mg, Level &L, int prec, bool x_zero, hipStream_t s) {
   return HPMG_OK;
 }
 
-int cycle(hpmg_mg_s *mg, int l, hipStream_t s) {
+// One cycle from level l down; started: the restriction has made the level's first
+// smoothing step.
+int cycle(hpmg_mg_s *mg, int l, hipStream_t s, bool started = false) {
   int st;
   const int prec = prec_of(mg);
   Level &L = mg->lv[l];
@@ -397,12 +408,19 @@ int cycle(hpmg_mg_s *mg, int l, hipStream_t s) {
     return st;
   }
   Level &C = mg->lv[l + 1];
-  if ((st = chebyshev(mg, L, prec, true, s))) return st;
+  if ((st = chebyshev(mg, L, prec, started ? First::done : First::from_zero, s))) return st;
   if ((st = smooth(mg, L, prec, SMOOTH_RESIDUAL, 0.0, 0.0, s))) return st;
-  HPMG_HIP(launch_restrict(*L.op, *C.op, prec, L.r, C.b, s));
-  if ((st = cycle(mg, l + 1, s))) return st;
+  const bool smoothed = l + 2 < (int)mg->lv.size();
+  Smooth start{};
+  if (smoothed) {
+    double theta, delta;
+    cheb_interval(mg, C, &theta, &delta);
+    start = smoother(C, SMOOTH_START, 1.0 / theta, 0.0);
+  }
+  HPMG_HIP(launch_restrict(*L.op, *C.op, prec, L.r, C.b, s, smoothed ? &start : nullptr));
+  if ((st = cycle(mg, l + 1, s, smoothed))) return st;
   HPMG_HIP(launch_prolong_add(*C.op, *L.op, prec, C.x, L.x, s));
-  return chebyshev(mg, L, prec, false, s);
+  return chebyshev(mg, L, prec, First::from_x, s);
 }
 
 int vcycle(hpmg_mg_s *mg, const double *r, double *z, hipStream_t s) {

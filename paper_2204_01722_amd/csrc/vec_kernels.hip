@@ -152,22 +152,6 @@ __global__ __launch_bounds__(BS) void k_dot2_partial(int64_t n, const T *__restr
 }
 
 template <typename T>
-__global__ __launch_bounds__(BS) void k_jacobi_dot_partial(int64_t n, const T *__restrict__ dinv,
-                                                           const T *__restrict__ r, T *__restrict__ z,
-                                                           double *__restrict__ partial) {
-  double v[2] = {0.0, 0.0};
-  T a[STRIDES], b[STRIDES];
-  strided(n, [&](int k, int64_t i) { a[k] = r[i], b[k] = dinv[i]; },
-          [&](int k, int64_t i) {
-            const T ri = a[k], zi = b[k] * ri;
-            z[i] = zi;
-            v[0] += (double)ri * (double)zi;
-            v[1] += (double)ri * (double)ri;
-          });
-  block_store<2>(v, partial);
-}
-
-template <typename T>
 __global__ __launch_bounds__(BS) void k_dot_pair_partial(int64_t n, const T *__restrict__ z,
                                                          const T *__restrict__ a, const T *__restrict__ b,
                                                          double *__restrict__ partial) {
@@ -190,19 +174,47 @@ __global__ __launch_bounds__(BS) void k_sum_partial(int64_t n, const double *__r
   block_store<1>(v, partial);
 }
 
+// PCG start from x = 0 (x null: the iterate is not formed): r = b, z = D^-1 r, p = z,
+// partials of r.z and r.r.
+template <typename T>
+__global__ __launch_bounds__(BS) void k_pcg_start(int64_t n, const T *__restrict__ dinv, const T *__restrict__ b,
+                                                  T *__restrict__ x, T *__restrict__ r, T *__restrict__ z,
+                                                  T *__restrict__ p, double *__restrict__ partial) {
+  double v[2] = {0.0, 0.0};
+  T vb[STRIDES], vi[STRIDES];
+  strided(n, [&](int k, int64_t i) { vb[k] = b[i], vi[k] = dinv[i]; },
+          [&](int k, int64_t i) {
+            const T ri = vb[k], zi = vi[k] * ri;
+            if (x) x[i] = T(0);
+            r[i] = ri;
+            z[i] = zi;
+            p[i] = zi;
+            v[0] += (double)ri * (double)zi;
+            v[1] += (double)ri * (double)ri;
+          });
+  block_store<2>(v, partial);
+}
+
+// Sum of RED_BLOCKS values by a workgroup of as many threads in a fixed tree (thread 0).
+__device__ __forceinline__ double block_tree(double v) {
+  __shared__ double s[RED_BLOCKS];
+  s[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = RED_BLOCKS / 2; w > 0; w >>= 1) {
+    if (threadIdx.x < (unsigned)w) s[threadIdx.x] += s[threadIdx.x + w];
+    __syncthreads();
+  }
+  const double t = s[0];
+  __syncthreads();
+  return t;
+}
+
 // One workgroup: out[k] = sum of partial[k * nb .. k * nb + nb) in a fixed tree.
 __global__ __launch_bounds__(RED_BLOCKS) void k_final(const double *__restrict__ partial, int nb, int nv,
                                                       double *__restrict__ out) {
-  __shared__ double s[RED_BLOCKS];
   for (int k = 0; k < nv; ++k) {
-    s[threadIdx.x] = threadIdx.x < (unsigned)nb ? partial[k * nb + threadIdx.x] : 0.0;
-    __syncthreads();
-    for (int w = RED_BLOCKS / 2; w > 0; w >>= 1) {
-      if (threadIdx.x < (unsigned)w) s[threadIdx.x] += s[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[k] = s[0];
-    __syncthreads();
+    const double t = block_tree(threadIdx.x < (unsigned)nb ? partial[k * nb + threadIdx.x] : 0.0);
+    if (threadIdx.x == 0) out[k] = t;
   }
 }
 
@@ -249,10 +261,13 @@ __device__ __forceinline__ double block_reduce_fixed(const double *__restrict__ 
 // test runs on the device: dir2 raises sc[SC_STOP], after which every kernel of later
 // iterations returns at once, so the host can queue many iterations and read the
 // scalars rarely.
-__global__ void k_pcg_begin(double *__restrict__ sc) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    sc[8] = sc[2];
-    sc[SC_RR0] = sc[3];
+// The scalars of the start from k_pcg_start's partials.
+__global__ __launch_bounds__(RED_BLOCKS) void k_pcg_begin(const double *__restrict__ partial,
+                                                          double *__restrict__ sc) {
+  const double rz = block_tree(partial[threadIdx.x]), rr = block_tree(partial[RED_BLOCKS + threadIdx.x]);
+  if (threadIdx.x == 0) {
+    sc[2] = sc[8] = rz;
+    sc[3] = sc[SC_RR0] = rr;
     sc[5] = 0.0;
     sc[SC_STOP] = 0.0;
     sc[SC_COUNT] = 0.0;
@@ -946,8 +961,15 @@ hipError_t launch_fcg_dir(int64_t n, double *sc, int it, const double *z, double
   return hipGetLastError();
 }
 
-hipError_t launch_pcg_begin(double *sc, hipStream_t s) {
-  k_pcg_begin<<<1, 64, 0, s>>>(sc);
+hipError_t launch_pcg_start(int prec, int64_t n, const void *dinv, const void *b, void *x, void *r, void *z, void *p,
+                            double *partial, double *sc, hipStream_t s) {
+  if (prec == HPMG_F64)
+    k_pcg_start<double><<<RED_BLOCKS, BS, 0, s>>>(n, (const double *)dinv, (const double *)b, (double *)x,
+                                                  (double *)r, (double *)z, (double *)p, partial);
+  else
+    k_pcg_start<float><<<RED_BLOCKS, BS, 0, s>>>(n, (const float *)dinv, (const float *)b, (float *)x, (float *)r,
+                                                 (float *)z, (float *)p, partial);
+  k_pcg_begin<<<1, RED_BLOCKS, 0, s>>>(partial, sc);
   return hipGetLastError();
 }
 
@@ -1107,18 +1129,6 @@ hipError_t launch_dot2(int prec, int64_t n, const void *x, const void *y, const 
   else
     k_dot2_partial<float><<<RED_BLOCKS, BS, 0, s>>>(n, (const float *)x, (const float *)y, (const float *)z,
                                                     partial);
-  k_final<<<1, RED_BLOCKS, 0, s>>>(partial, RED_BLOCKS, 2, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_jacobi_dot(int prec, int64_t n, const void *dinv, const void *r, void *z, double *partial,
-                             double *out, hipStream_t s) {
-  if (prec == HPMG_F64)
-    k_jacobi_dot_partial<double><<<RED_BLOCKS, BS, 0, s>>>(n, (const double *)dinv, (const double *)r,
-                                                           (double *)z, partial);
-  else
-    k_jacobi_dot_partial<float><<<RED_BLOCKS, BS, 0, s>>>(n, (const float *)dinv, (const float *)r, (float *)z,
-                                                          partial);
   k_final<<<1, RED_BLOCKS, 0, s>>>(partial, RED_BLOCKS, 2, out);
   return hipGetLastError();
 }
