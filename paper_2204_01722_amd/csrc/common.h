@@ -245,14 +245,10 @@ hipError_t launch_init_bc(int prec, int64_t n_nodes, const uint8_t *mask, const 
 hipError_t launch_cast_state(int64_t n, const double *a, float *b, hipStream_t s);
 hipError_t launch_dot(int prec, int64_t n, const void *x, const void *y, double *partial,
                       double *out, hipStream_t s);
-hipError_t launch_dot2(int prec, int64_t n, const void *x, const void *y, const void *z,
-                       double *partial, double *out, hipStream_t s);  // out[0]=x.y, out[1]=z.z
 hipError_t launch_sum(int64_t n, const double *x, double *partial, double *out, hipStream_t s);
 hipError_t launch_axpby(int prec, int64_t n, double a, const void *x, double b, void *y, hipStream_t s);
 hipError_t launch_waxpby(int prec, int64_t n, double a, const void *x, double b, const void *y,
                          void *w, hipStream_t s);  // w = a x + b y
-hipError_t launch_cg_update(int prec, int64_t n, double alpha, const void *p, const void *q, void *x,
-                            const void *r_in, void *r_out, hipStream_t s);  // x += a p; r_out = r_in - a q
 hipError_t launch_dot_pair(int prec, int64_t n, const void *z, const void *a, const void *b,
                            double *partial, double *out, hipStream_t s);  // out = {z.a, z.b}
 hipError_t launch_cast(int64_t n, int to_prec, const void *x, void *y, hipStream_t s);

@@ -73,15 +73,6 @@ __global__ void k_waxpby(int64_t n, T a, const T *__restrict__ x, T b, const T *
 }
 
 template <typename T>
-__global__ void k_cg_update(int64_t n, T alpha, const T *__restrict__ p, const T *__restrict__ q,
-                            T *__restrict__ x, const T *__restrict__ rin, T *__restrict__ rout) {
-  GRID_STRIDE(i, n) {
-    x[i] += alpha * p[i];
-    rout[i] = rin[i] - alpha * q[i];
-  }
-}
-
-template <typename T>
 __global__ void k_recip(int64_t n, T *__restrict__ x) {
   GRID_STRIDE(i, n) { x[i] = T(1) / x[i]; }
 }
@@ -135,20 +126,6 @@ __global__ __launch_bounds__(BS) void k_dot_partial(int64_t n, const T *__restri
   strided(n, [&](int k, int64_t i) { a[k] = x[i], b[k] = y[i]; },
           [&](int k, int64_t) { v[0] += (double)a[k] * (double)b[k]; });
   block_store<1>(v, partial);
-}
-
-template <typename T>
-__global__ __launch_bounds__(BS) void k_dot2_partial(int64_t n, const T *__restrict__ x,
-                                                     const T *__restrict__ y, const T *__restrict__ z,
-                                                     double *__restrict__ partial) {
-  double v[2] = {0.0, 0.0};
-  T a[STRIDES], b[STRIDES], c[STRIDES];
-  strided(n, [&](int k, int64_t i) { a[k] = x[i], b[k] = y[i], c[k] = z[i]; },
-          [&](int k, int64_t) {
-            v[0] += (double)a[k] * (double)b[k];
-            v[1] += (double)c[k] * (double)c[k];
-          });
-  block_store<2>(v, partial);
 }
 
 template <typename T>
@@ -813,6 +790,9 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
   int32_t *ids = reinterpret_cast<int32_t *>(zh + 3 * a.max_halo);
   if (tid == 0) sh.lost = 0;
   for (int u = tid; u < nh; u += CP_NT) ids[u] = a.halo_ids[h0 + u];
+  // zero entries of rows past the end and of padding slots meet p[0], which nothing else
+  // writes where the first row's node is shared with the workgroup before
+  for (int u = tid; u < a.rows; u += CP_NT) p[u] = T(0);
   T A[RPT][3 * W], x[RPT], r[RPT], z[RPT], di[RPT], po[RPT];
   uint32_t off[RPT][(W + 1) / 2];  // first entry of each column's direction, two to a word
   bool whole[RPT];                 // the row's node is all in this workgroup
@@ -1088,15 +1068,6 @@ hipError_t launch_waxpby(int prec, int64_t n, double a, const void *x, double b,
                                                        (float *)w)));
 }
 
-hipError_t launch_cg_update(int prec, int64_t n, double alpha, const void *p, const void *q, void *x,
-                            const void *rin, void *rout, hipStream_t s) {
-  DISPATCH(prec,
-           (k_cg_update<double><<<grid_for(n), BS, 0, s>>>(n, alpha, (const double *)p, (const double *)q,
-                                                           (double *)x, (const double *)rin, (double *)rout)),
-           (k_cg_update<float><<<grid_for(n), BS, 0, s>>>(n, (float)alpha, (const float *)p, (const float *)q,
-                                                          (float *)x, (const float *)rin, (float *)rout)));
-}
-
 hipError_t launch_recip(int prec, int64_t n, void *x, hipStream_t s) {
   DISPATCH(prec, (k_recip<double><<<grid_for(n), BS, 0, s>>>(n, (double *)x)),
            (k_recip<float><<<grid_for(n), BS, 0, s>>>(n, (float *)x)));
@@ -1118,18 +1089,6 @@ hipError_t launch_dot(int prec, int64_t n, const void *x, const void *y, double 
   else
     k_dot_partial<float><<<RED_BLOCKS, BS, 0, s>>>(n, (const float *)x, (const float *)y, partial);
   k_final<<<1, RED_BLOCKS, 0, s>>>(partial, RED_BLOCKS, 1, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_dot2(int prec, int64_t n, const void *x, const void *y, const void *z, double *partial,
-                       double *out, hipStream_t s) {
-  if (prec == HPMG_F64)
-    k_dot2_partial<double><<<RED_BLOCKS, BS, 0, s>>>(n, (const double *)x, (const double *)y, (const double *)z,
-                                                     partial);
-  else
-    k_dot2_partial<float><<<RED_BLOCKS, BS, 0, s>>>(n, (const float *)x, (const float *)y, (const float *)z,
-                                                    partial);
-  k_final<<<1, RED_BLOCKS, 0, s>>>(partial, RED_BLOCKS, 2, out);
   return hipGetLastError();
 }
 
