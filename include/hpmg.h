@@ -295,7 +295,10 @@ int hpmg_mg_set_state(hpmg_mg mg, const double *u, void *stream);
  * l = 0 .. n_levels-2).  Synchronises `stream` (reads CG coefficients). */
 int hpmg_mg_setup(hpmg_mg mg, const double *const *seeds, void *stream);
 /* z = M^{-1} r (one V-cycle, zero initial guess), double in and out.
- * The coarse solve's stopping test runs on the device; the host queues its iterations
+ * The coarse solve's stopping test runs on the device.  An assembled coarsest level whose
+ * rows fit the device's registers is solved in one launch, read back once; its workgroups
+ * wait for each other with a bound, and a solve that runs into it (another process holding
+ * the device) is made again iteration by iteration.  Otherwise the host queues iterations
  * in batches (the first as long as the previous coarse solve) and synchronises once per
  * batch to read the outcome, or never with coarse_fixed_its. */
 int hpmg_mg_vcycle(hpmg_mg mg, const double *r, double *z, void *stream);

@@ -237,8 +237,7 @@ __device__ __forceinline__ double block_reduce_fixed(const double *__restrict__ 
 // 9 so that no workgroup overwrites a value another one still reads.  The convergence
 // test runs on the device: dir2 raises sc[SC_STOP], after which every kernel of later
 // iterations returns at once, so the host can queue many iterations and read the
-// scalars rarely.
-// The scalars of the start from k_pcg_start's partials.
+// scalars rarely.  k_pcg_begin: the scalars of the start from k_pcg_start's partials.
 __global__ __launch_bounds__(RED_BLOCKS) void k_pcg_begin(const double *__restrict__ partial,
                                                           double *__restrict__ sc) {
   const double rz = block_tree(partial[threadIdx.x]), rr = block_tree(partial[RED_BLOCKS + threadIdx.x]);
