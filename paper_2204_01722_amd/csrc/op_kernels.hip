@@ -391,6 +391,17 @@ bool keep_records(int64_t E, int P) {
   return (double)E * P * P * P * 3 * sizeof(T) <= 160.0 * (1 << 20);
 }
 
+// A residual's state of more than 240 MiB, which all but fills the 256 MiB last-level cache,
+// streams out past it (MODE 8 of k_jacobian_lines); a smaller one goes there with plain
+// stores, where the next pass finds it.  Plain stores of a state beyond the cache are bound
+// by its write-back: residual alone 308 us on 34^3 Q4 elements (644 MB), 117 on 25^3 (256 MB)
+// and 123 on 43^3 Q2 ones (289 MB) against 234, 99 and 107; with a Jacobian action behind it
+// 179 against 173 us on 25^3, but 160 against 164 on 41^3 Q2 elements (251 MB) and 117
+// against 123 on 22^3 Q4 ones (174 MB).
+inline bool stream_state(int64_t tiles, int Q) {
+  return (double)tiles * NSTATE * field_stride(Q) * sizeof(double) > 240.0 * (1 << 20);
+}
+
 __device__ __forceinline__ double mat_mu(double mu0, const double *mu_e, int64_t e) {
   return mu_e ? mu_e[e] : mu0;
 }
@@ -571,6 +582,8 @@ __device__ __forceinline__ void store_tile_records(T *__restrict__ ev, int64_t t
 // MODE 4: the residual (du is u, unmasked; T = double): kinematics and the Kirchhoff
 // flux from the geometry (W, dxi/dX), the 16-scalar state written to state_out when it
 // is given, non-positive or non-finite J raised in flags.
+// MODE 8: the residual of MODE 4 with a state too large for the last-level cache: whole
+// lines of it leave with nontemporal stores (stream_state).
 // MODE 5: the Jacobian with the linearisation recomputed at u (T = double or float; u
 // is converted to T): u and du go through the forward stages side by side (half the
 // barriers of one after the other, and nothing of u to keep in registers meanwhile); the
@@ -594,8 +607,9 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
     double *__restrict__ state_out, unsigned *__restrict__ flags, const double *__restrict__ u,
     double *__restrict__ mub, double *__restrict__ lamb) {
   constexpr bool STATE = MODE == 0 || MODE == 6, TWO = MODE == 5 || MODE == 7, VJP = MODE == 6 || MODE == 7;
+  constexpr bool RES = MODE == 4 || MODE == 8;
   constexpr int NH = MODE == 2 ? 16 : MODE == 3 ? 19 : 9;
-  static_assert(MODE != 4 || std::is_same<T, double>::value, "the residual form is FP64");
+  static_assert(!RES || std::is_same<T, double>::value, "the residual form is FP64");
   if (stop && *stop != 0.0) return;  // a stopped PCG (uniform over the grid)
   constexpr int Q2 = Q * Q, Q3 = Q2 * Q, P3 = P * P * P, ET = QT<Q>::ET, NQ = QT<Q>::NQ, NT = QT<Q>::NT;
   // Per element: v [3][Q^3] (du, then its values at the points, then the z-derivative
@@ -659,7 +673,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
       vu[2 * Q3 + qn] = (T)u2;
     }
     // u is taken whole (the residual); du has its constrained components zeroed
-    const uint32_t bc = MODE == 4 ? 0u : (w >> EMAP_BC_SHIFT);
+    const uint32_t bc = RES ? 0u : (w >> EMAP_BC_SHIFT);
     v[qn] = (bc & 1u) ? T(0) : x0;
     v[Q3 + qn] = ((bc >> 1) & 1u) ? T(0) : x1;
     v[2 * Q3 + qn] = ((bc >> 2) & 1u) ? T(0) : x2;
@@ -677,7 +691,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
       for (int f = 0; f < 9; ++f) hv[f] = __builtin_nontemporal_load(h + f * NQ);
 #pragma unroll
       for (int f = 0; f < 10; ++f) hv[9 + f] = __builtin_nontemporal_load(h + (16 + f) * NQ);
-    } else if constexpr (MODE == 4 || TWO) {
+    } else if constexpr (RES || TWO) {
       const double *g = geo + tile * NGEO * NQ + tq;
 #pragma unroll
       for (int f = 0; f < NGEO; ++f) gv[f] = __builtin_nontemporal_load(g + f * NQ);
@@ -742,6 +756,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
   __syncthreads();
   // Quadrature function, one thread per point, flux written over the gradient
   // (components k = 0, 1 in G, k = 2 in v).
+  double so[MODE == 8 ? NSTATE : 1] = {};
   if (live) {
     T Gq[3][3], f[3][3];
 #pragma unroll
@@ -833,7 +848,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
           lds[el * ELS + PS + Q3 + q] = W * (T)k.logJ * (M[0][0] + M[1][1] + M[2][2]);
         }
       }
-    } else if constexpr (MODE == 4) {
+    } else if constexpr (RES) {
       double D[3][3];
 #pragma unroll
       for (int k = 0; k < 3; ++k)
@@ -843,17 +858,23 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
       kinematics(Gq, D, mat_mu(mu0, mu_e, e), mat_mu(lam0, lam_e, e), k);
       if (!(k.Jm1 > -1.0)) atomicOr(flags, k.Jm1 == k.Jm1 ? HPMG_FLAG_NONPOSITIVE_J : HPMG_FLAG_NONFINITE);
       residual_qf(k, gv[0], f);
-      if (state_out) {
+      if (MODE == 8 || state_out) {
         // sqrt(W) dxi/dx, tau, lambda log J (the weight rides in the scaled dxi/dx)
-        double *so = state_out + tile * NSTATE * NQ + tq;
         const double sw = sqrt(gv[0]);
+        double *o = state_out + tile * NSTATE * NQ + tq;
+        auto put = [&](int i, double x) {
+          if constexpr (MODE == 8)
+            so[i] = x;
+          else
+            o[i * NQ] = x;
+        };
 #pragma unroll
         for (int kk = 0; kk < 3; ++kk)
 #pragma unroll
-          for (int j = 0; j < 3; ++j) so[(kk * 3 + j) * NQ] = sw * k.A[kk][j];
+          for (int j = 0; j < 3; ++j) put(kk * 3 + j, sw * k.A[kk][j]);
 #pragma unroll
-        for (int m = 0; m < 6; ++m) so[(9 + m) * NQ] = k.tau[m];
-        so[15 * NQ] = k.c;
+        for (int m = 0; m < 6; ++m) put(9 + m, k.tau[m]);
+        put(15, k.c);
       }
     } else {
       jacobian_qf_initial<MODE == 2>(Gq, gv, hv, mat_mu(mu0, mu_e, e), mat_mu(lam0, lam_e, e), f);
@@ -863,6 +884,14 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
       G[(i * 2) * Q3 + q] = f[i][0];
       G[(i * 2 + 1) * Q3 + q] = f[i][1];
       v[i * Q3 + q] = f[i][2];
+    }
+  }
+  if constexpr (MODE == 8) {
+    // the padding too (zeros), so that every line goes out whole
+    if (tq < NQ) {
+      double *o = state_out + tile * NSTATE * NQ + tq;
+#pragma unroll
+      for (int i = 0; i < NSTATE; ++i) __builtin_nontemporal_store(so[i], o + i * NQ);
     }
   }
   __syncthreads();
@@ -1820,13 +1849,20 @@ hipError_t launch_qdata(const hpmg_op_s &op, const double *X, hipStream_t s) {
 // Residual: the element kernel writes element records, the node-centric assembly pass
 // sums them (deterministic).
 hipError_t launch_residual(const hpmg_op_s &op, const double *u, double *r, bool store, hipStream_t s) {
+  const bool stream = store && stream_state(op.tiles, op.Q);
 #define X(p, q)                                                                                  \
   if (op.P == p && op.Q == q) {                                                                  \
-    lines_launch<double, p, q, 4>((unsigned)op.tiles, s, keep_records<double>(op.E, p), op.emap, u,            \
-                                  (const double *)nullptr, op.geo, (const double *)nullptr, op.tab64, op.mu,      \
-                                  op.lam, op.mu_e, op.lam_e, (double *)op.evec, op.E, (const double *)nullptr,    \
-                                  store ? op.state64 : nullptr, op.flags, (const double *)nullptr,                \
-                                  (double *)nullptr, (double *)nullptr);                                          \
+    const auto go = [&](auto mode) {                                                             \
+      lines_launch<double, p, q, decltype(mode)::value>(                                         \
+          (unsigned)op.tiles, s, keep_records<double>(op.E, p), op.emap, u, (const double *)nullptr, op.geo,      \
+          (const double *)nullptr, op.tab64, op.mu, op.lam, op.mu_e, op.lam_e, (double *)op.evec, op.E,           \
+          (const double *)nullptr, store ? op.state64 : nullptr, op.flags, (const double *)nullptr,               \
+          (double *)nullptr, (double *)nullptr);                                                 \
+    };                                                                                           \
+    if (stream)                                                                                  \
+      go(std::integral_constant<int, 8>());                                                      \
+    else                                                                                         \
+      go(std::integral_constant<int, 4>());                                                      \
     hipError_t e = hipGetLastError();                                                            \
     if (e != hipSuccess) return e;                                                               \
     return assemble<double>(op, nullptr, r, s);                                                  \

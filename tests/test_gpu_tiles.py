@@ -69,3 +69,20 @@ def test_diagonal_and_adjoint_at_tile_edges(p, mode):
                 assert rel(t2n(g), r) < TOL[prec]
             alone = op.residual_vjp(ut, ww, mode=mode, precision=prec, want_params=False)
             assert alone[1] is None and torch.equal(alone[0], got[0])
+
+
+@pytest.mark.parametrize("p, n", [(4, (24, 25, 25)), (4, (25, 25, 25)), (2, (43, 43, 43)), (3, (32, 32, 31))])
+def test_state_on_both_sides_of_the_cache(p, n):
+    """A residual whose state stays in the last-level cache or streams past it (more than
+    240 MiB): the residual of the form without a state bit for bit, and a stored linearisation
+    that acts as the recomputed one, also in a ragged last tile."""
+    import torch
+    print_case("state_stream", n=n, p=p)
+    m, H = _hierarchy(n, (p,))
+    op = H.fine
+    u, du = (torch.from_numpy(v).cuda() for v in (inputs.config1_u(m, amplitude=0.05),
+                                                  inputs.random_vector(m.n_nodes, 5)))
+    r = op.residual(u, store_state=True)
+    assert torch.equal(r, op.residual(u, store_state=False))
+    assert rel(t2n(op.jacobian(du)), t2n(op.jacobian(du, mode="recompute", u=u))) < TOL["f64"]
+    assert op.query_flags() == 0
