@@ -402,6 +402,22 @@ inline bool stream_state(int64_t tiles, int Q) {
   return (double)tiles * NSTATE * field_stride(Q) * sizeof(double) > 240.0 * (1 << 20);
 }
 
+// Inside a V-cycle or an eigenvalue estimate (Finish sm or pq), a linearisation of 48 to 168
+// MiB is loaded with plain loads: it stays in the 256 MiB last-level cache beside the records
+// and vectors, and the next action (a smoothing step, an iteration, the level below) reads it
+// there.  Plain against nontemporal loads, us an apply repeated on one state: Q4 FP64 on 20^3
+// elements (131 MB) 37.7 against 41.3, on 22^3 (174 MB) 46.9 against 51.7, FP32 on 20^3 (66
+// MB) 25.2 against 27.2, on 25^3 (128 MB) 40.0 against 43.6, Q2 FP32 on 43^3 (145 MB) 41.9
+// against 46.1; on either side they lose: FP32 on 16^3 (34 MB) 17.5 against 16.7, on 28^3
+// (180 MB) 58.4 against 57.3, FP64 on 25^3 (256 MB) 80.6 against 73.2, on 34^3 (644 MB) 208
+// against 170.  A single action keeps the nontemporal loads: with the states of five
+// operators in turn, 20^3 FP64 takes 42.1 us with them and 47.3 with plain ones.
+template <typename T>
+bool keep_state(int64_t tiles, int Q) {
+  const double b = (double)tiles * NSTATE * field_stride(Q) * sizeof(T);
+  return b >= 48.0 * (1 << 20) && b <= 168.0 * (1 << 20);
+}
+
 __device__ __forceinline__ double mat_mu(double mu0, const double *mu_e, int64_t e) {
   return mu_e ? mu_e[e] : mu0;
 }
@@ -584,6 +600,8 @@ __device__ __forceinline__ void store_tile_records(T *__restrict__ ev, int64_t t
 // is given, non-positive or non-finite J raised in flags.
 // MODE 8: the residual of MODE 4 with a state too large for the last-level cache: whole
 // lines of it leave with nontemporal stores (stream_state).
+// MODE 9: MODE 0 with plain loads of a state that stays in the last-level cache from one
+// action to the next (keep_state).
 // MODE 5: the Jacobian with the linearisation recomputed at u (T = double or float; u
 // is converted to T): u and du go through the forward stages side by side (half the
 // barriers of one after the other, and nothing of u to keep in registers meanwhile); the
@@ -606,7 +624,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
     const double *__restrict__ lam_e, T *__restrict__ ev, int64_t E, const double *__restrict__ stop,
     double *__restrict__ state_out, unsigned *__restrict__ flags, const double *__restrict__ u,
     double *__restrict__ mub, double *__restrict__ lamb) {
-  constexpr bool STATE = MODE == 0 || MODE == 6, TWO = MODE == 5 || MODE == 7, VJP = MODE == 6 || MODE == 7;
+  constexpr bool KEEP = MODE == 9, APPLY = MODE == 0 || KEEP, STATE = APPLY || MODE == 6, TWO = MODE == 5 || MODE == 7, VJP = MODE == 6 || MODE == 7;
   constexpr bool RES = MODE == 4 || MODE == 8;
   constexpr int NH = MODE == 2 ? 16 : MODE == 3 ? 19 : 9;
   static_assert(!RES || std::is_same<T, double>::value, "the residual form is FP64");
@@ -682,7 +700,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
     if constexpr (STATE) {
       const T *s = state + tile * NSTATE * NQ + tq;
 #pragma unroll
-      for (int f = 0; f < NSTATE; ++f) sv[f] = __builtin_nontemporal_load(s + f * NQ);
+      for (int f = 0; f < NSTATE; ++f) sv[f] = KEEP ? s[f * NQ] : __builtin_nontemporal_load(s + f * NQ);
       if (par) gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W
     } else if constexpr (MODE == 3) {
       gv[0] = __builtin_nontemporal_load(geo + tile * NGEO * NQ + tq);  // W only
@@ -765,7 +783,7 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
       Gq[c][1] = G[(c * 2 + 1) * Q3 + q];
       Gq[c][2] = v[c * Q3 + q];
     }
-    if constexpr (MODE == 0) {
+    if constexpr (APPLY) {
       T A[3][3], tau[6];
 #pragma unroll
       for (int k = 0; k < 3; ++k)
@@ -1874,7 +1892,7 @@ hipError_t launch_residual(const hpmg_op_s &op, const double *u, double *r, bool
 
 template <typename T, int P, int Q>
 static hipError_t jacobian_pq(const hpmg_op_s &op, const hpmg_op_s &f, int mode, const double *u, const T *du,
-                              T *ev, const double *stop, hipStream_t s) {
+                              T *ev, const double *stop, bool again, hipStream_t s) {
   const T *state = std::is_same<T, double>::value ? (const T *)f.state64 : (const T *)f.state32;
   const T *tab = std::is_same<T, double>::value ? (const T *)op.tab64 : (const T *)op.tab32;
   const bool keep = keep_records<T>(op.E, P);
@@ -1894,8 +1912,15 @@ static hipError_t jacobian_pq(const hpmg_op_s &op, const hpmg_op_s &f, int mode,
     }
   }
   if (mode == HPMG_STORED) {
-    lines_launch<T, P, Q, 0>(g, s, keep, op.emap, du, state, nullptr, nullptr, tab, f.mu, f.lam, f.mu_e, f.lam_e,
-                             ev, op.E, stop, nullptr, nullptr, nullptr, nullptr, nullptr);
+    const auto go = [&](auto m) {
+      lines_launch<T, P, Q, decltype(m)::value>(g, s, keep, op.emap, du, state, nullptr, nullptr, tab, f.mu, f.lam,
+                                                f.mu_e, f.lam_e, ev, op.E, stop, nullptr, nullptr, nullptr, nullptr,
+                                                nullptr);
+    };
+    if (again && keep_state<T>(op.tiles, Q))
+      go(std::integral_constant<int, 9>());
+    else
+      go(std::integral_constant<int, 0>());
   } else {
     lines_launch<T, P, Q, 5>(g, s, keep, op.emap, du, (const T *)nullptr, op.geo, (const double *)nullptr, tab,
                              op.mu, op.lam, op.mu_e, op.lam_e, ev, op.E, (const double *)nullptr,
@@ -1954,7 +1979,7 @@ static hipError_t jacobian_t(const hpmg_op_s &op, int mode, const double *u, con
   }
   hipError_t e = hipErrorInvalidValue;
 #define X(p, q) \
-  if (op.P == p && op.Q == q) e = jacobian_pq<T, p, q>(op, f, mode, u, du, ev, fin.stop, s);
+  if (op.P == p && op.Q == q) e = jacobian_pq<T, p, q>(op, f, mode, u, du, ev, fin.stop, fin.sm || fin.pq, s);
   HPMG_PQ_LIST(X)
 #undef X
   if (e != hipSuccess) return e;

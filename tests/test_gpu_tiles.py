@@ -86,3 +86,22 @@ def test_state_on_both_sides_of_the_cache(p, n):
     assert torch.equal(r, op.residual(u, store_state=False))
     assert rel(t2n(op.jacobian(du)), t2n(op.jacobian(du, mode="recompute", u=u))) < TOL["f64"]
     assert op.query_flags() == 0
+
+
+@pytest.mark.parametrize("n", [17, 25])
+def test_vcycle_state_kept_in_cache(n):
+    """V-cycles that load the linearisation so that it stays in the cache (48 to 168 MiB: FP64
+    on 17^3, FP32 on 25^3) against the other precision, whose size takes the other loads."""
+    import torch
+    from paper_2204_01722_amd.binding import PMG
+    print_case("vcycle_kept_state", n=n)
+    m, H = _hierarchy((n, n, n), (4, 2, 1))
+    H.fine.residual(torch.from_numpy(inputs.config1_u(m, amplitude=0.05)).cuda(), store_state=True)
+    free = 1.0 - H.masks[0].reshape(-1)
+    r = torch.from_numpy((inputs.random_vector(m.n_nodes, 23).reshape(-1) * free).reshape(-1, 3)).cuda()
+    out = {}
+    for prec in ("f64", "f32"):
+        pmg = PMG(H.ops, precision=prec, coarse_fixed_its=8)
+        pmg.setup(H.seeds(7))
+        out[prec] = t2n(pmg.vcycle(r))
+    assert rel(out["f32"], out["f64"]) < 1e-4  # the solver tests' bound for FP32 V-cycles
