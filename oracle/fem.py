@@ -253,7 +253,7 @@ def residual_vjp(disc: Disc, u, w, mu, lam, mask=None, chunk=4096):
     """Vector-Jacobian product of the (masked) residual ``r(u; mu_e, lambda_e)``:
     returns ``(u_bar, mu_bar, lambda_bar)`` with ``u_bar = (dr/du)^T w`` written as the
     explicit transpose contraction ``sum W (grad w)_{iJ} A_{iJkL} dphi_b/dX_L`` and
-    ``mu_bar_e = sum_q W grad(w):(F - F^{-T})``,
+    ``mu_bar_e = sum_q W grad(w):(F - F^{-T})`` (the difference formed as in ``piola``),
     ``lambda_bar_e = sum_q W log J grad(w):F^{-T}`` (P is linear in mu and lambda)."""
     E, N = disc.n_elem, disc.n_nodes
     mu, lam = _mat(mu, E), _mat(lam, E)
@@ -273,7 +273,7 @@ def residual_vjp(disc: Disc, u, w, mu, lam, mask=None, chunk=4096):
         F = np.eye(3) + H
         FinvT = np.swapaxes(np.linalg.inv(F), -1, -2)
         logJ = np.log1p(j_minus_1(H))
-        mub[sl] = np.einsum("eq,eqiJ,eqiJ->e", W, Gw, F - FinvT)
+        mub[sl] = np.einsum("eq,eqiJ,eqiJ->e", W, Gw, H + np.swapaxes(H, -1, -2) @ FinvT)
         lamb[sl] = np.einsum("eq,eq,eqiJ,eqiJ->e", W, logJ, Gw, FinvT)
     return ub, mub, lamb
 

@@ -344,3 +344,21 @@ def test_uniaxial_stress_by_traction():
     exact = m.coords * np.array([l1 - 1.0, l2 - 1.0, l2 - 1.0])
     np.testing.assert_allclose(u, exact, atol=1e-10)
     assert l1 > 1.05 and l2 < 1.0
+
+
+def test_vjp_mu_bar_at_small_strain_against_50_digits():
+    """Affine u and w on a regular box: mu_bar_e = V_e grad(w) : (F - F^-T) exactly.  At
+    strains of 1e-6 a difference of F and F^-T formed in FP64 is off by 1e-10."""
+    mpmath = pytest.importorskip("mpmath")
+    mpmath.mp.dps = 50
+    m = inputs.box_mesh((2, 1, 1), 1)
+    d = fem.make_disc(m.coords, m.elem_nodes, 2)
+    rng = np.random.default_rng(3)
+    G = rng.normal(size=(3, 3))
+    for size in (1e-1, 1e-3, 1e-6):
+        H = size * rng.normal(size=(3, 3))
+        F = mpmath.matrix([[mpmath.mpf(float(H[i, j])) + (1 if i == j else 0) for j in range(3)] for i in range(3)])
+        D = F - (F ** -1).T
+        exact = mpmath.fsum(mpmath.mpf(float(G[i, j])) * D[i, j] for i in range(3) for j in range(3)) / 2
+        got = fem.residual_vjp(d, m.coords @ H.T, m.coords @ G.T, np.ones(2), np.ones(2))[1]
+        assert np.abs(got / float(exact) - 1.0).max() < 1e-13
