@@ -860,13 +860,18 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
       c[s][0] = (double)po[s] * (double)q[s];
     }
     ok = cp_sum<1, RPT, true, false>(a, epoch++, c, pq, sh, [](int, int) {});
-    if (!ok || !(pq[0] > 0.0)) break;  // breakdown: x as it is
-    const T al = (T)(rz / pq[0]);
+    if (!ok) break;
+    // a breakdown ends with a step of length zero, as k_pcg_update2 makes it: a direction
+    // that is not finite shows in x
+    const bool broke = !(pq[0] > 0.0);
+    const T al = broke ? T(0) : (T)(rz / pq[0]);
+#pragma unroll
+    for (int s = 0; s < RPT; ++s) x[s] += al * po[s];
+    if (broke) break;
     U *const zw = it & 1 ? z0 : z1, *const zo = it & 1 ? z1 : z0;
 #pragma unroll
     for (int s = 0; s < RPT; ++s) {
       const int row = tid + s * CP_NT;
-      x[s] += al * po[s];
       r[s] = r[s] - al * q[s];
       z[s] = di[s] * r[s];
       if (row < rows) {
