@@ -297,10 +297,15 @@ int hpmg_mg_setup(hpmg_mg mg, const double *const *seeds, void *stream);
 /* z = M^{-1} r (one V-cycle, zero initial guess), double in and out.
  * The coarse solve's stopping test runs on the device.  An assembled coarsest level whose
  * rows fit the device's registers is solved in one launch, read back once; its workgroups
- * wait for each other with a bound, and a solve that runs into it (another process holding
- * the device) is made again iteration by iteration.  Otherwise the host queues iterations
- * in batches (the first as long as the previous coarse solve) and synchronises once per
- * batch to read the outcome, or never with coarse_fixed_its. */
+ * wait for each other with a bound (hpmg_mg_set_coarse_wait), and a solve that runs into it
+ * (another stream or process holding compute units) is made again iteration by iteration, as
+ * are the handle's next 32 (after further losses in a row 64, 128, up to 4096) coarse solves
+ * before one launch is tried again.  The two forms give the same bits where the blocks are
+ * row-major and the level has at most 131,072 rows; elsewhere they group their sums
+ * differently, so that a solve given up there changes the last bits of z.
+ * Otherwise the host queues iterations in batches (the first as long as the previous coarse
+ * solve) and synchronises once per batch to read the outcome, or never with
+ * coarse_fixed_its. */
 int hpmg_mg_vcycle(hpmg_mg mg, const double *r, double *z, void *stream);
 /* lambda_max estimate of a level and the last coarse-solve iteration count. */
 int hpmg_mg_info(hpmg_mg mg, int level, double *lambda_max, int *last_coarse_its);
@@ -309,6 +314,13 @@ int hpmg_mg_info(hpmg_mg mg, int level, double *lambda_max, int *last_coarse_its
  * iterations, out[2] setups, out[3 + l] stored-mode operator applies on level l
  * (l < 8; smoothing, residuals, coarse iterations and eigenvalue estimates). */
 int hpmg_mg_stats(hpmg_mg mg, int64_t *out);
+/* Coarse solves since creation (host only): out[0] made in one launch, out[1] made launch
+ * by launch, out[2] given up in one launch after a wait (each made again and counted in
+ * out[1]). */
+int hpmg_mg_coarse_stats(hpmg_mg mg, int64_t *out);
+/* Longest wait, in seconds (0 to 10, default 0.1), of a workgroup for another in a coarse
+ * solve made in one launch; 0: whatever is not there at the first look is given up. */
+int hpmg_mg_set_coarse_wait(hpmg_mg mg, double seconds);
 
 /* a14: flexible CG (FP64) on the fine operator, preconditioned by one V-cycle of
  * `mg`.  Solves J x = b from the x passed in; stops at ||b - Jx|| <= rtol ||b - J x0||.

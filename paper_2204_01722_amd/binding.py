@@ -91,6 +91,8 @@ _SIGS = {
     "hpmg_mg_vcycle": ([_VP, _VP, _VP, _VP], _I),
     "hpmg_mg_info": ([_VP, _I, C.POINTER(_D), C.POINTER(_I)], _I),
     "hpmg_mg_stats": ([_VP, _VP], _I),
+    "hpmg_mg_coarse_stats": ([_VP, _VP], _I),
+    "hpmg_mg_set_coarse_wait": ([_VP, _D], _I),
     "hpmg_fcg_solve": ([_VP, _VP, _VP, _VP, _D, _I, C.POINTER(_I), C.POINTER(_D), _VP], _I),
     "hpmg_newton_default_params": ([C.POINTER(NewtonParams)], None),
     "hpmg_state_initial_bytes": ([_VP, C.POINTER(C.c_size_t)], _I),
@@ -538,6 +540,17 @@ class PMG:
         v = list(arr)
         return {"vcycles": v[0], "coarse_its": v[1], "setups": v[2],
                 "applies_per_level": v[3:3 + len(self.levels)]}
+
+    def coarse_stats(self):
+        """Coarse solves so far: made in one launch, made launch by launch, and given up in
+        one launch after a wait (and made again)."""
+        arr = (C.c_int64 * 3)()
+        _check(lib().hpmg_mg_coarse_stats(self.h, C.cast(arr, C.c_void_p)))
+        return dict(zip(("one_launch", "launches", "given_up"), arr))
+
+    def set_coarse_wait(self, seconds):
+        """Longest wait of a workgroup for another in a coarse solve made in one launch."""
+        _check(lib().hpmg_mg_set_coarse_wait(self.h, float(seconds)))
 
     def fcg(self, b, x=None, rtol=1e-8, maxit=500):
         b = self._fine_vec(b, "b")

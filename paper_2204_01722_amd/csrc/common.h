@@ -184,10 +184,11 @@ hipError_t launch_ell_pcg_apply(int prec, bool node_major, int64_t nn, int W, co
 // node all of whose rows the workgroup owns, else rows + 3 k for node halo_ids[k] of its
 // list halo_ids[halo_off[g] .. halo_off[g + 1]).  slots: coarse_pcg_slots(nn) doubles.
 // Stops as dir2 does, or after maxit iterations; sets sc[SC_COUNT], and sc[SC_LOST] if a
-// workgroup waited longer than a bounded time for another (x is then not to be used).
+// workgroup waited longer than `wait` for another (x is then not to be used).
 struct CoarsePcg {
   int64_t nn;
   int rows, groups, W, max_halo, maxit;
+  long long wait;  // in ticks of the device's 100 MHz clock (COARSE_PCG_TICKS a second)
   bool node_major;
   double rtol2;
   const void *vals;
@@ -199,6 +200,7 @@ struct CoarsePcg {
   double *slots, *sc;
 };
 constexpr int COARSE_PCG_W = 27;  // most columns of a row
+constexpr double COARSE_PCG_TICKS = 1e8;
 // Every workgroup posts its sums in this many places, so that few read the same lines.
 constexpr int COARSE_PCG_COPIES = 8;
 int coarse_pcg_max_rows(int prec);

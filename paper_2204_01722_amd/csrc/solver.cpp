@@ -21,6 +21,11 @@ namespace {
 inline size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 inline hipStream_t S(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
+// Solves made by launches after one that was given up in one launch.  Giving up costs its wait
+// (100 ms) and a solve by launches 1-4 ms, so that a device that stays busy loses about half
+// of its coarse time at first and a few per cent in the end.
+constexpr int CP_RETRY = 32, CP_RETRY_MAX = 4096;
+
 struct Level {
   hpmg_op_s *op = nullptr;
   int64_t n = 0;  // scalars (3 * nodes)
@@ -64,7 +69,10 @@ struct hpmg_mg_s {
   // The same level split over workgroups for the one-launch PCG (cp_groups = 0: not split):
   // cp_rows rows each, the halo nodes of every workgroup and each column's place in it.
   int cp_groups = 0, cp_rows = 0, cp_max_halo = 0;
-  bool cp_lost = false;  // its workgroups once waited in vain: not tried again on this handle
+  // A solve whose workgroups wait longer than cp_wait seconds is given up; after the k-th in
+  // a row, CP_RETRY * 2^(k - 1) solves (at most CP_RETRY_MAX) are made by launches.
+  double cp_wait = 0.1;
+  int cp_skip = 0, cp_retry = CP_RETRY;
   std::vector<int32_t> cp_off_host, cp_ids_host;
   std::vector<uint16_t> cp_cols_host;
   int32_t *cp_off = nullptr, *cp_ids = nullptr;
@@ -72,6 +80,7 @@ struct hpmg_mg_s {
   double *cp_slots = nullptr;
   // counters since creation: V-cycles, coarse iterations, operator applies per level
   int64_t n_vcycles = 0, n_coarse_its = 0, n_setups = 0;
+  int64_t n_one_launch = 0, n_launches = 0, n_given_up = 0;  // coarse solves by how they were made
   int64_t n_applies[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 };
 
@@ -241,6 +250,7 @@ int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hi
   a.W = mg->ell_w;
   a.max_halo = mg->cp_max_halo;
   a.maxit = maxit;
+  a.wait = (long long)(mg->cp_wait * COARSE_PCG_TICKS);
   a.node_major = mg->ell_node_major;
   a.rtol2 = rtol * rtol;
   a.vals = mg->ell_vals;
@@ -258,9 +268,13 @@ int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hi
   HPMG_HIP(launch_coarse_pcg(prec, a, s));
   if ((st = read_scalars(mg, SC_LOST + 1, s))) return st;
   if (mg->host[SC_LOST] != 0.0) {
-    mg->cp_lost = true;
+    mg->n_given_up++;
+    mg->cp_skip = mg->cp_retry;
+    mg->cp_retry = std::min(2 * mg->cp_retry, CP_RETRY_MAX);
     return HPMG_OK;
   }
+  mg->cp_retry = CP_RETRY;
+  mg->n_one_launch++;
   *its_out = (int)mg->host[SC_COUNT];
   const size_t l = &L - mg->lv.data();
   if (l < 8) mg->n_applies[l] += *its_out;
@@ -397,12 +411,17 @@ int cycle(hpmg_mg_s *mg, int l, hipStream_t s, bool started = false) {
   if (l + 1 == (int)mg->lv.size()) {
     int its = 0;
     bool done = false;
-    if (mg->cp_groups > 0 && !mg->cp_lost && mg->prm.coarse_fixed_its <= 0 && blocks_current(mg) &&
-        (st = pcg_one_launch(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, s, &its, &done)))
+    const bool split = mg->cp_groups > 0 && mg->prm.coarse_fixed_its <= 0 && blocks_current(mg);
+    if (split && mg->cp_skip > 0)
+      mg->cp_skip--;
+    else if (split &&
+             (st = pcg_one_launch(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, s, &its, &done)))
       return st;
-    if (!done)
+    if (!done) {
+      mg->n_launches++;
       st = pcg_device(mg, L, prec, mg->prm.coarse_rtol, mg->prm.coarse_maxit, mg->prm.coarse_fixed_its,
                       mg->last_coarse_its, 4, s, &its);
+    }
     mg->last_coarse_its = its;
     mg->n_coarse_its += its;
     return st;
@@ -886,6 +905,22 @@ int hpmg_mg_stats(hpmg_mg mg, int64_t *out) {
   out[1] = mg->n_coarse_its;
   out[2] = mg->n_setups;
   for (int l = 0; l < 8; ++l) out[3 + l] = mg->n_applies[l];
+  return HPMG_OK;
+}
+
+int hpmg_mg_coarse_stats(hpmg_mg mg, int64_t *out) {
+  if (!mg || !out) return fail(HPMG_ERR_ARG, "mg_coarse_stats: null argument");
+  out[0] = mg->n_one_launch;
+  out[1] = mg->n_launches;
+  out[2] = mg->n_given_up;
+  return HPMG_OK;
+}
+
+int hpmg_mg_set_coarse_wait(hpmg_mg mg, double seconds) {
+  if (!mg) return fail(HPMG_ERR_ARG, "mg_set_coarse_wait: null multigrid handle");
+  if (!(seconds >= 0.0) || seconds > 10.0)
+    return fail(HPMG_ERR_ARG, "mg_set_coarse_wait: 0 to 10 seconds expected");
+  mg->cp_wait = seconds;
   return HPMG_OK;
 }
 

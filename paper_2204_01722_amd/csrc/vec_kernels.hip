@@ -548,7 +548,6 @@ struct CpBits<float> {
   static __device__ __forceinline__ U of(float v) { return __float_as_uint(v == v ? v : __builtin_nanf("")); }
   static __device__ __forceinline__ float value(U u) { return __uint_as_float(u); }
 };
-constexpr long long CP_WAIT_TICKS = 10000000;  // 100 ms of the 100 MHz clock
 
 template <typename U>
 __device__ __forceinline__ U agent_load(const U *p) {
@@ -617,7 +616,7 @@ struct CpShared {
 // before it is used again: all have read it then (when a workgroup posts epoch e, all have
 // read epoch e - 2), and an ACK call (every other one) lies in between, which posts only
 // after all that its workgroup stored before has been acknowledged.
-// false: a wait took over 100 ms (every thread of the workgroup agrees).
+// false: a wait took over a.wait (every thread of the workgroup agrees).
 template <int NV, int RPT, bool ACK, bool FIRST, typename F>
 __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const double (&in)[RPT][NV], double (&out)[NV],
                                        CpShared<RPT> &sh, F meanwhile) {
@@ -676,7 +675,7 @@ __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const doub
           x[k] = B::value(q[k]);
         }
         if (all) return;
-        if (wall_clock64() - t0 > CP_WAIT_TICKS) {
+        if (wall_clock64() - t0 > a.wait) {
           sh.lost = 1;
           return;
         }
@@ -735,7 +734,7 @@ __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const doub
 // value that is still empty has not arrived).
 template <typename T>
 __device__ __forceinline__ void cp_fetch(const typename CpBits<T>::U *__restrict__ zx, const int32_t *ids, T *zh,
-                                         int nh, int *lost, int first, int count) {
+                                         int nh, int *lost, long long wait, int first, int count) {
   using B = CpBits<T>;
   constexpr int NF = sizeof(T) == 4 ? 2 : 1;  // nodes whose loads are in flight together
   const long long t0 = wall_clock64();
@@ -758,7 +757,7 @@ __device__ __forceinline__ void cp_fetch(const typename CpBits<T>::U *__restrict
 #pragma unroll
         for (int k = 0; k < 3; ++k) all = all && q[f][k] != B::EMPTY;
       if (all) break;
-      if (wall_clock64() - t0 > CP_WAIT_TICKS) {
+      if (wall_clock64() - t0 > wait) {
         *lost = 1;
         break;
       }
@@ -828,8 +827,8 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
   __syncthreads();  // ids
   int epoch = 0, it = 0;
   double sum[2], pq[1];
-  bool ok = cp_sum<2, RPT, false, true>(a, epoch++, v, sum, sh, [z0, ids, zh, nh, lost = &sh.lost](int t, int c) {
-    cp_fetch<T>(z0, ids, zh, nh, lost, t, c);
+  bool ok = cp_sum<2, RPT, false, true>(a, epoch++, v, sum, sh, [z0, ids, zh, nh, lost = &sh.lost, wait = a.wait](int t, int c) {
+    cp_fetch<T>(z0, ids, zh, nh, lost, wait, t, c);
   });
   double rz = sum[0], beta = 0.0;
   const double rr0 = sum[1];
@@ -881,8 +880,8 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
       v[s][0] = (double)r[s] * (double)z[s];
       v[s][1] = (double)r[s] * (double)r[s];
     }
-    ok = cp_sum<2, RPT, false, false>(a, epoch++, v, sum, sh, [zw, ids, zh, nh, lost = &sh.lost](int t, int c) {
-      cp_fetch<T>(zw, ids, zh, nh, lost, t, c);
+    ok = cp_sum<2, RPT, false, false>(a, epoch++, v, sum, sh, [zw, ids, zh, nh, lost = &sh.lost, wait = a.wait](int t, int c) {
+      cp_fetch<T>(zw, ids, zh, nh, lost, wait, t, c);
     });
     if (!ok) break;
     ++it;

@@ -156,3 +156,9 @@ def test_mg_parameters_rejected_before_any_level_is_used(L):
         assert call(**kw) == 1, kw
         assert L.hpmg_last_error().startswith(b"mg_create:"), kw
         assert out.value is None
+
+
+def test_coarse_solve_calls_reject_null_handles(L):
+    out = (C.c_int64 * 3)()
+    assert L.hpmg_mg_coarse_stats(None, out) == 1 and L.hpmg_last_error().startswith(b"mg_coarse_stats:")
+    assert L.hpmg_mg_set_coarse_wait(None, 0.1) == 1 and L.hpmg_last_error().startswith(b"mg_set_coarse_wait:")
