@@ -300,9 +300,12 @@ int hpmg_mg_setup(hpmg_mg mg, const double *const *seeds, void *stream);
  * wait for each other with a bound (hpmg_mg_set_coarse_wait), and a solve that runs into it
  * (another stream or process holding compute units) is made again iteration by iteration, as
  * are the handle's next 32 (after further losses in a row 64, 128, up to 4096) coarse solves
- * before one launch is tried again.  The two forms give the same bits where the blocks are
- * row-major and the level has at most 131,072 rows; elsewhere they group their sums
- * differently, so that a solve given up there changes the last bits of z.
+ * before one launch is tried again.  Solves in one launch of several threads share a device's
+ * compute units: one that does not fit beside the others waits on the host, within the same
+ * bound, until one of them has been read back, and is else made iteration by iteration.  The
+ * two forms give the same bits where the blocks are row-major and the level has at most
+ * 131,072 rows; elsewhere they group their sums differently, so that such a solve changes
+ * the last bits of z.
  * Otherwise the host queues iterations in batches (the first as long as the previous coarse
  * solve) and synchronises once per batch to read the outcome, or never with
  * coarse_fixed_its. */
@@ -319,7 +322,8 @@ int hpmg_mg_stats(hpmg_mg mg, int64_t *out);
  * out[1]). */
 int hpmg_mg_coarse_stats(hpmg_mg mg, int64_t *out);
 /* Longest wait, in seconds (0 to 10, default 0.1), of a workgroup for another in a coarse
- * solve made in one launch; 0: whatever is not there at the first look is given up. */
+ * solve made in one launch, and of the host for room on the device; 0: whatever is not there
+ * at the first look is given up. */
 int hpmg_mg_set_coarse_wait(hpmg_mg mg, double seconds);
 
 /* a14: flexible CG (FP64) on the fine operator, preconditioned by one V-cycle of

@@ -3,16 +3,14 @@
 // in the library's kernels; the host reads back the few scalars that decide control
 // flow (CG coefficients, norms) through a pinned buffer.
 #include <algorithm>
-#include <condition_variable>
 #include <cstdint>
 #include <cmath>
 #include <cstdio>
-#include <map>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "common.h"
+#include "resident.h"
 
 using namespace hpmg;
 
@@ -191,43 +189,6 @@ bool blocks_current(const hpmg_mg_s *mg) {
   return mg->ell_ready && mg->ell_version == src->state_version;
 }
 
-// Workgroups of the one-launch coarse solve wait for each other, so all of a launch must
-// be resident together.  At most one per compute unit and device is let in at a time:
-// a launch that would exceed that waits here until earlier ones have ended (another
-// thread's; they are read back before they leave).
-class ResidentGroups {
- public:
-  ResidentGroups(int device, int groups, int limit) : device_(device), groups_(groups) {
-    std::unique_lock<std::mutex> lock(mutex());
-    freed().wait(lock, [&] { return in_use()[device_] + groups_ <= limit; });
-    in_use()[device_] += groups_;
-  }
-  ~ResidentGroups() {
-    {
-      std::lock_guard<std::mutex> lock(mutex());
-      in_use()[device_] -= groups_;
-    }
-    freed().notify_all();
-  }
-  ResidentGroups(const ResidentGroups &) = delete;
-  ResidentGroups &operator=(const ResidentGroups &) = delete;
-
- private:
-  static std::mutex &mutex() {
-    static std::mutex m;
-    return m;
-  }
-  static std::condition_variable &freed() {
-    static std::condition_variable c;
-    return c;
-  }
-  static std::map<int, int> &in_use() {
-    static std::map<int, int> m;
-    return m;
-  }
-  int device_, groups_;
-};
-
 int compute_units(int *device, int *units) {
   HPMG_HIP(hipGetDevice(device));
   HPMG_HIP(hipDeviceGetAttribute(units, hipDeviceAttributeMultiprocessorCount, *device));
@@ -235,8 +196,9 @@ int compute_units(int *device, int *units) {
 }
 
 // The coarse solve of pcg_device (fixed = 0, nothing recorded) in one launch.  *done stays
-// false, and the caller solves again the other way, if the workgroups did not find each
-// other in time (another process held compute units).
+// false, and the caller solves the other way, if other threads' solves left no room for its
+// workgroups in time, or if these did not find each other in time (another stream or process
+// held compute units).
 int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hipStream_t s, int *its_out,
                    bool *done) {
   int st, dev = 0, cus = 0;
@@ -264,7 +226,8 @@ int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hi
   a.z[1] = L.t;
   a.slots = mg->cp_slots;
   a.sc = mg->scal;
-  ResidentGroups resident(dev, a.groups, cus);
+  ResidentGroups resident(dev, a.groups, cus, mg->cp_wait);
+  if (!resident.admitted()) return HPMG_OK;
   HPMG_HIP(launch_coarse_pcg(prec, a, s));
   if ((st = read_scalars(mg, SC_LOST + 1, s))) return st;
   if (mg->host[SC_LOST] != 0.0) {
