@@ -177,18 +177,24 @@ _MODES = {STORED: STORED, "stored": STORED, RECOMPUTE: RECOMPUTE, "recompute": R
           "initial_tuned": INITIAL_TUNED, CURRENT_20: CURRENT_20, "current_20": CURRENT_20}
 
 
-def _prec(p):
+def _named(table, v, what):
     try:
-        return _PRECS[p]
+        return table[v]
     except (KeyError, TypeError):
-        raise ValueError(f"bad precision {p!r}") from None
+        pass
+    # a value that equals a name without hashing like it: an array or tensor of one entry
+    for name, code in table.items():
+        if v == name:
+            return code
+    raise ValueError(f"bad {what} {v!r}")
+
+
+def _prec(p):
+    return _named(_PRECS, p, "precision")
 
 
 def _mode(m):
-    try:
-        return _MODES[m]
-    except (KeyError, TypeError):
-        raise ValueError(f"bad mode {m!r}") from None
+    return _named(_MODES, m, "mode")
 
 
 def _dtype(prec):
