@@ -294,20 +294,24 @@ int hpmg_mg_set_state(hpmg_mg mg, const double *u, void *stream);
  * iterations on the caller's rough vectors seeds[l] (device double [n_nodes_l][3],
  * l = 0 .. n_levels-2).  Synchronises `stream` (reads CG coefficients). */
 int hpmg_mg_setup(hpmg_mg mg, const double *const *seeds, void *stream);
-/* z = M^{-1} r (one V-cycle, zero initial guess), double in and out.
+/* z = M^{-1} r (one V-cycle, zero initial guess), double in and out.  With an FP64 V-cycle
+ * the finest level works on r and z themselves (on copies if they overlap), so a call that
+ * fails leaves z undefined.
  * The coarse solve's stopping test runs on the device.  An assembled coarsest level whose
- * rows fit the device's registers is solved in one launch, read back once; its workgroups
- * wait for each other with a bound (hpmg_mg_set_coarse_wait), and a solve that runs into it
- * (another stream or process holding compute units) is made again iteration by iteration, as
- * are the handle's next 32 (after further losses in a row 64, 128, up to 4096) coarse solves
- * before one launch is tried again.  Solves in one launch of several threads share a device's
- * compute units: one that does not fit beside the others waits on the host, within the same
- * bound, until one of them has been read back, and is else made iteration by iteration.  The
- * two forms give the same bits where the blocks are row-major and the level has at most
- * 131,072 rows; elsewhere they group their sums differently, so that such a solve changes
- * the last bits of z.
- * Otherwise the host queues iterations in batches (the first as long as the previous coarse
- * solve) and synchronises once per batch to read the outcome, or never with
+ * rows fit the device's registers (512 a compute unit in FP64, 1024 in FP32: 131,072 and
+ * 262,144 on 256 units), at most 27 nodes wide and numbered so that the nodes which a
+ * workgroup shares with others fit 60 KiB, is solved in one launch, read back once; its
+ * workgroups wait for each other with a bound (hpmg_mg_set_coarse_wait), and a solve that
+ * runs into it (another stream or process holding compute units) is made again iteration
+ * by iteration, as are the handle's next 32 (after further losses in a row 64, 128, up to
+ * 4096) coarse solves before one launch is tried again.  Solves in one launch of several
+ * threads share a device's compute units: one that does not fit beside the others waits on
+ * the host, within the same bound, until one of them has been read back, and is else made
+ * iteration by iteration.  The two forms give the same bits where the blocks are row-major
+ * and the level has at most 131,072 rows; elsewhere they group their sums differently, so
+ * that such a solve changes the last bits of z.
+ * Otherwise the host queues iterations in batches (the first as long as the previous
+ * coarse solve) and synchronises once per batch to read the outcome, or never with
  * coarse_fixed_its. */
 int hpmg_mg_vcycle(hpmg_mg mg, const double *r, double *z, void *stream);
 /* lambda_max estimate of a level and the last coarse-solve iteration count. */

@@ -362,7 +362,7 @@ __device__ __forceinline__ void jacobian_qf_initial(const double (&G)[3][3], con
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.  Give
 // every XCD a contiguous range of tiles so neighbouring elements (which share nodes,
-// hence gathered values and atomic targets) run under the same L2.
+// hence gathered values) run under the same L2.
 __device__ __forceinline__ int64_t xcd_tile() {
   constexpr unsigned NX = 8;
   const unsigned b = blockIdx.x, G = gridDim.x;
@@ -375,13 +375,18 @@ __device__ __forceinline__ int64_t xcd_tile() {
 // assembly writes its output from LDS in whole-line nontemporal sweeps.  Records of up
 // to 160 MiB (keep_records) are stored with plain stores, so that they stay in the
 // 256 MB last-level cache for the assembly that follows; larger ones stream out with
-// nontemporal stores.  Measured per apply, plain against nontemporal record stores:
-// Q2 on 43^3 elements (52 MB of records) 87.2 against 92.5 us, Q4 on 34^3 (118 MB) 188
-// against 201 us, Q2 on 60^3 (140 MB) 220 against 235 us; Q4 on 40^3 (192 MB) 354
-// against 331 us, Q4 on 46^3 (292 MB) 549 against 515 us, Q2 on 86^3 (412 MB) 766
-// against 724 us, Q4 on 68^3 (943 MB) 1750 against 1643 us; per-node stores: Q4 34^3
-// 217 us, Q2 43^3 88.4 us, Q2 86^3 785 us.  In FP32 the per-node stores were as fast or
-// faster.
+// nontemporal stores.  Measured, us an apply, plain / nontemporal record stores:
+//                                     one operator repeated   four operators in turn
+//   Q2 on 43^3 elements (52 MB)              90 / 93                 87 / 89
+//   Q4 on 34^3 (118 MB)                     194 / 203               205 / 195
+//   Q2 on 60^3 (140 MB)                     212 / 225               236 / 232
+//   Q4 on 37^3 (152 MB)                     261 / 258               262 / 259
+//   Q4 on 40^3 (192 MB)                     329 / 318               330 / 317
+//   Q2 on 72^3 (242 MB)                     418 / 400               415 / 403
+// The line is drawn for one operator, as in a Krylov solve, where it lies near 145 MB; for
+// operators in turn it lies between 52 and 118 MB.  An earlier form of the kernels with
+// per-node stores: Q4 34^3 217 us against 188, Q2 43^3 88.4 against 87.2, Q2 86^3 785 against
+// 724.  In FP32 the per-node stores were as fast or faster.
 template <typename T>
 __host__ __device__ constexpr bool sweep_records(int P) {
   return std::is_same<T, double>::value && (P == 5 || P == 3);
@@ -394,10 +399,19 @@ bool keep_records(int64_t E, int P) {
 // A residual's state of more than 240 MiB, which all but fills the 256 MiB last-level cache,
 // streams out past it (MODE 8 of k_jacobian_lines); a smaller one goes there with plain
 // stores, where the next pass finds it.  Plain stores of a state beyond the cache are bound
-// by its write-back: residual alone 308 us on 34^3 Q4 elements (644 MB), 117 on 25^3 (256 MB)
-// and 123 on 43^3 Q2 ones (289 MB) against 234, 99 and 107; with a Jacobian action behind it
-// 179 against 173 us on 25^3, but 160 against 164 on 41^3 Q2 elements (251 MB) and 117
-// against 123 on 22^3 Q4 ones (174 MB).
+// by its write-back: residual alone 308 us on 34^3 Q4 elements (614 MiB) against 234
+// streaming.  Measured, us, residual and a Jacobian action behind it, plain / streaming:
+//                                one operator repeated   three in turn
+//   Q4 on 20^3 (125 MiB)                94 / 101            104 / 99
+//   22^3 (166 MiB)                     120 / 127            132 / 125
+//   23^3 (190 MiB)                     139 / 142            154 / 143
+//   24^3 (216 MiB)                     161 / 158            174 / 164
+//   25^3 (244 MiB)                     180 / 176            195 / 187
+//   Q2 on 40^3 (222 MiB)               152 / 155            165 / 154
+//   41^3 (240 MiB)                     163 / 167            178 / 168
+//   43^3 (276 MiB)                     185 / 186            202 / 194
+// The line is drawn for one operator: there it lies near 200 MiB at Q4 and near 276 at Q2, and
+// 240 is in between; with operators in turn streaming wins at every size measured.
 inline bool stream_state(int64_t tiles, int Q) {
   return (double)tiles * NSTATE * field_stride(Q) * sizeof(double) > 240.0 * (1 << 20);
 }
@@ -405,13 +419,14 @@ inline bool stream_state(int64_t tiles, int Q) {
 // Inside a V-cycle or an eigenvalue estimate (Finish sm or pq), a linearisation of 48 to 168
 // MiB is loaded with plain loads: it stays in the 256 MiB last-level cache beside the records
 // and vectors, and the next action (a smoothing step, an iteration, the level below) reads it
-// there.  Plain against nontemporal loads, us an apply repeated on one state: Q4 FP64 on 20^3
-// elements (131 MB) 37.7 against 41.3, on 22^3 (174 MB) 46.9 against 51.7, FP32 on 20^3 (66
-// MB) 25.2 against 27.2, on 25^3 (128 MB) 40.0 against 43.6, Q2 FP32 on 43^3 (145 MB) 41.9
-// against 46.1; on either side they lose: FP32 on 16^3 (34 MB) 17.5 against 16.7, on 28^3
-// (180 MB) 58.4 against 57.3, FP64 on 25^3 (256 MB) 80.6 against 73.2, on 34^3 (644 MB) 208
-// against 170.  A single action keeps the nontemporal loads: with the states of five
-// operators in turn, 20^3 FP64 takes 42.1 us with them and 47.3 with plain ones.
+// there.  Measured, us a V-cycle Q4 -> Q2 -> Q1 with four coarse iterations, plain /
+// nontemporal loads: FP64 on 12^3 elements (28 MiB) 320 / 320, 14^3 (43 MiB) 384 / 378, 16^3 (64
+// MiB) 439 / 453, 20^3 (125 MiB) 632 / 654, 22^3 (166 MiB) 820 / 810, 24^3 (216 MiB) 1050 / 991;
+// FP32 on 14^3 (22 MiB) 292 / 295, 18^3 (46 MiB) 382 / 385, 20^3 (63 MiB) 439 / 454, 25^3 (122
+// MiB) 668 / 685, 28^3 (172 MiB) 924 / 902: below 48 MiB the two are equal within the runs'
+// spread, from 166 MiB on plain loads lose.  A single action keeps the nontemporal loads: with
+// the states of five operators in turn, 20^3 FP64 takes 42.1 us with them and 47.3 with plain
+// ones.
 template <typename T>
 bool keep_state(int64_t tiles, int Q) {
   const double b = (double)tiles * NSTATE * field_stride(Q) * sizeof(T);
@@ -498,8 +513,10 @@ __global__ __launch_bounds__(QT<Q>::NT) void k_qdata(const uint32_t *__restrict_
 // i1 + Q i2 + Q^2 i3, so the interpolation stages can work in place.  The pointwise
 // work (state loads, quadrature function, gather, records) keeps the one-thread-per-
 // point mapping and the tile layout of the other kernels.
-// Bound by memory: at Q4, 34^3 elements, FP64, the 868 MB of an apply's element kernel pass
-// in 139-150 us (6 TB/s) where one input is used again and in 155-180 where inputs rotate.
+// Bound by memory: at Q4, 34^3 elements, FP64, the 858 MB of an apply's element kernel pass
+// in 137-144 us (6.1 TB/s) where one operator is used again and in 152 where four take turns;
+// the assembly's 213 MB then take 53 us instead of 33, its records and lists no longer being in
+// the last-level cache.
 // ------------------------------------------------------------------------------------
 
 // First frame offset and stride of line r of a stage along DIR whose lines run over
@@ -1624,7 +1641,8 @@ __global__ void k_build_emap(const int32_t *__restrict__ en, const uint8_t *__re
 
 // Sum of node n's element records in the fixed order of its incidence list, the loads of
 // four records in flight together: one at a time, Q2 applies on 43^3 elements took 84.6 us
-// in FP64 and 49.2 in FP32 against 81.2 and 45.7, Q4 on 34^3 208 and 118.5 against 203 and 117.
+// in FP64 and 49.2 in FP32 against 81.2 and 45.7, Q4 on 34^3 208 and 118.5 against 203 and 117
+// (operators in turn).
 template <typename T>
 __device__ __forceinline__ void node_sum(const int32_t *__restrict__ off, const int32_t *__restrict__ inc,
                                          const T *__restrict__ ev, int64_t n, T (&a)[3]) {
@@ -1697,8 +1715,8 @@ __global__ __launch_bounds__(256) void k_assemble_staged(int64_t N, const int32_
 
 // The same node sums (A in, in itself on constrained components) finished as a step of the
 // Chebyshev smoother instead of being stored, so that A in is neither written nor read
-// again and a launch falls away (a V-cycle on 20^3 Q4 elements 1085 -> 979 us in FP64 and
-// 820 -> 750 in FP32, with node_sum's loads):
+// again and a launch falls away (a V-cycle on 20^3 Q4 elements, one right-hand side, 1085 ->
+// 979 us in FP64 and 820 -> 750 in FP32, node_sum's four-wide loads included):
 //   SMOOTH_STEP:  in = d: r -= D^-1 A d; d = c1 d + c2 r; x += d
 //   SMOOTH_FIRST: in = x: r = D^-1 (b - A x); d = c1 r; x += d
 //   SMOOTH_RESIDUAL: in = x: r = b - A x

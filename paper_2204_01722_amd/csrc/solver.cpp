@@ -477,8 +477,9 @@ int build_ell_structure(hpmg_mg_s *mg) {
 }
 
 // Splits the assembled coarsest level over the workgroups of the one-launch PCG; leaves
-// cp_groups = 0 where it does not fit (more rows than the device's compute units hold in
-// registers, rows wider than a hexahedral mesh's, or halos that do not fit in LDS).
+// cp_groups = 0 where it does not fit: more rows than the device's compute units hold in
+// registers, rows wider than a hexahedral mesh's, or a node numbering without bands, whose
+// workgroups share more nodes with others than 60 KiB of LDS (of the compute unit's 160) take.
 int build_coarse_split(hpmg_mg_s *mg) {
   const int64_t nn = mg->lv.back().n / 3, n3 = 3 * nn;
   const int W = mg->ell_w, prec = prec_of(mg);

@@ -521,11 +521,15 @@ __global__ __launch_bounds__(BS) void k_ell_pcg_nodes(int64_t nn, int W, const i
 // what remains of an iteration is two sums over the grid, each a store and a load through
 // the memory side (about 1.5 us), the neighbours' z fetched while the first is under way,
 // and 81 LDS reads a row.  Measured per iteration, launch to launch: 11^3 nodes 24 -> 4.4 us
-// (FP64), 21^3 23.6 -> 5.8 us (FP64), 26^3 25 -> 6.8 us (FP32); a whole V-cycle on 20^3 Q4
-// elements 1587 -> 917 us in FP64 and 1278 -> 680 us in FP32.
+// (FP64), 21^3 23.6 -> 5.8 us (FP64), 26^3 25 -> 6.8 us (FP32); a whole V-cycle Q4 -> Q2 -> Q1 to
+// a coarse tolerance of 1e-3, by launches against one launch: 20^3 elements FP64 998 -> 666 us
+// with a right-hand side of 17 coarse iterations, 2857 -> 1140 with one of 97; FP32 776 -> 470 and
+// 2429 -> 889; 25^3 FP32 1085 -> 709 (19) and 3164 -> 1206 (110).
 // 512 rows a workgroup and not fewer, since the sums cost more with every workgroup that
-// posts and reads them (21^3 nodes: 55 workgroups 191 us a solve, 127 221, 251 275); the
-// same sums in the same order as the launches' kernels, so the results are the same bits.
+// posts and reads them (21^3 nodes: 55 workgroups 191 us a solve, 127 221, 251 275).  The sums
+// are taken over blocks of 256 rows, in the order of the launches' kernels, so that row-major
+// blocks of at most 131,072 rows (the 512 x 256 threads of those kernels' grids) give the same
+// bits either way; beyond that, or with node-major blocks, the launches group them otherwise.
 constexpr int CP_NT = 512;
 constexpr int CP_RING = 8;  // sets of slots in rotation
 // What a slot or an exchanged value holds while it is empty: a NaN that no arithmetic
@@ -608,8 +612,8 @@ struct CpShared {
   int lost;
 };
 
-// Sums NV values over all rows, in the same order in every workgroup and in the order of
-// the launch-per-iteration form: a partial for every BS rows (four waves each), then these
+// Sums NV values over all rows, in the same order in every workgroup and, for row-major blocks
+// of at most 131,072 rows, in that of the launch-per-iteration form: a partial for every BS rows (four waves each), then these
 // as block_reduce_fixed_n does, or as k_final does for the FIRST sums.  Each workgroup
 // posts its partials in set `epoch` % 8 of the slots, and its first waves read everybody's
 // while the others run `meanwhile(first thread, threads)`.  A slot is emptied four epochs
