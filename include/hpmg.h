@@ -322,8 +322,8 @@ int hpmg_mg_info(hpmg_mg mg, int level, double *lambda_max, int *last_coarse_its
  * (l < 8; smoothing, residuals, coarse iterations and eigenvalue estimates). */
 int hpmg_mg_stats(hpmg_mg mg, int64_t *out);
 /* Coarse solves since creation (host only): out[0] made in one launch, out[1] made launch
- * by launch, out[2] given up in one launch after a wait (each made again and counted in
- * out[1]). */
+ * by launch (those that met a value that is not finite in one launch among them), out[2]
+ * given up in one launch after a wait (each made again and counted in out[1]). */
 int hpmg_mg_coarse_stats(hpmg_mg mg, int64_t *out);
 /* Longest wait, in seconds (0 to 10, default 0.1), of a workgroup for another in a coarse
  * solve made in one launch, and of the host for room on the device; 0: whatever is not there

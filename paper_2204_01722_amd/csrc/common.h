@@ -184,11 +184,12 @@ hipError_t launch_ell_pcg_apply(int prec, bool node_major, int64_t nn, int W, co
 // node all of whose rows the workgroup owns, else rows + 3 k for node halo_ids[k] of its
 // list halo_ids[halo_off[g] .. halo_off[g + 1]).  slots: coarse_pcg_slots(nn) doubles.
 // Stops as dir2 does, or after maxit iterations; sets sc[SC_COUNT], and sc[SC_LOST] if a
-// workgroup waited longer than `wait` for another (x is then not to be used).
+// workgroup waited longer than `wait` for another (x is then not to be used).  A breakdown
+// (p.q in sc[1], else 0 there) leaves x as it is, without update2's step of length zero.
 struct CoarsePcg {
   int64_t nn;
   int rows, groups, W, max_halo, maxit;
-  long long wait;  // in ticks of the device's 100 MHz clock (COARSE_PCG_TICKS a second)
+  long long wait;  // in ticks of the device's 100 MHz clock (COARSE_PCG_TICKS a second), below 2^31
   bool node_major;
   double rtol2;
   const void *vals;

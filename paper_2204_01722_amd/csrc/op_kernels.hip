@@ -630,7 +630,7 @@ __device__ __forceinline__ void store_tile_records(T *__restrict__ ev, int64_t t
 // counted from the last, most of which have no line of their own there.  With a thread per
 // point, all contractions out of LDS (two workgroups per compute unit) and one thread an
 // element summing the parameters, the FP64 product took 165 us on 20^3 Q4 elements and 53.5
-// on 23^3 Q3 ones, assembly included; this form 46.7 and 38.0 (recomputed 180 -> 61 and
+// on 23^3 Q3 ones, assembly included; this form 46-50 and 38-41 (recomputed 180 -> 61 and
 // 56 -> 49; MODE 7 is held to 128 registers for four waves per SIMD, 63 and 51 without).
 // SWEEP: how the records are stored (store_tile_records).
 template <typename T, int P, int Q, int MODE, int SWEEP>
@@ -1166,7 +1166,7 @@ __global__ void k_traction_load(const double *__restrict__ X, const int32_t *__r
 // tasks as in k_jacobian_lines, a task taking all pairs of its line so that the tables stay
 // in scalar registers, three barriers after the point stage.  One thread per point and
 // pair, with every contraction's operands read from LDS and 24 barriers, took 130-147 us for
-// 25^3 Q4 elements in FP64; this form 75-80, of which the 250 MB of state take 44 (summing
+// 25^3 Q4 elements in FP64; this form 70-83, of which the 250 MB of state take 44 (summing
 // the pairs that share an x table before the x stage saves another 8 us, but rounds
 // otherwise than before, which the coarse solves of a V-cycle amplify to 1e-9 and more).
 // ------------------------------------------------------------------------------------

@@ -197,8 +197,8 @@ int compute_units(int *device, int *units) {
 
 // The coarse solve of pcg_device (fixed = 0, nothing recorded) in one launch.  *done stays
 // false, and the caller solves the other way, if other threads' solves left no room for its
-// workgroups in time, or if these did not find each other in time (another stream or process
-// held compute units).
+// workgroups in time, if these did not find each other in time (another stream or process
+// held compute units), or if the solve met a value that is not finite.
 int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hipStream_t s, int *its_out,
                    bool *done) {
   int st, dev = 0, cus = 0;
@@ -237,6 +237,10 @@ int pcg_one_launch(hpmg_mg_s *mg, Level &L, int prec, double rtol, int maxit, hi
     return HPMG_OK;
   }
   mg->cp_retry = CP_RETRY;
+  // A breakdown on p.q that is not finite: the zero step with which the launches end it
+  // carries a direction that is not finite into x, so they make this solve.  (In the kernel
+  // that step, wherever it stood, cost the other solves 0.5 to 4 % in registers.)
+  if (!std::isfinite(mg->host[1])) return HPMG_OK;
   mg->n_one_launch++;
   *its_out = (int)mg->host[SC_COUNT];
   const size_t l = &L - mg->lv.data();

@@ -573,7 +573,7 @@ __global__ void k_coarse_begin(CoarsePcg a, int64_t n_slots) {
     z0[i] = B::EMPTY;
     z1[i] = B::EMPTY;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[SC_COUNT] = a.sc[SC_LOST] = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[1] = a.sc[SC_COUNT] = a.sc[SC_LOST] = 0.0;
 }
 
 // Sum over the wave in the order of wave_sum (lanes 32 apart, then 16, 8, 4, 2 and 1), in
@@ -613,8 +613,9 @@ struct CpShared {
 };
 
 // Sums NV values over all rows, in the same order in every workgroup and, for row-major blocks
-// of at most 131,072 rows, in that of the launch-per-iteration form: a partial for every BS rows (four waves each), then these
-// as block_reduce_fixed_n does, or as k_final does for the FIRST sums.  Each workgroup
+// of at most 131,072 rows, in that of the launch-per-iteration form: a partial for every BS
+// rows (four waves each), then these as block_reduce_fixed_n does, or as k_final does for the
+// FIRST sums.  Each workgroup
 // posts its partials in set `epoch` % 8 of the slots, and its first waves read everybody's
 // while the others run `meanwhile(first thread, threads)`.  A slot is emptied four epochs
 // before it is used again: all have read it then (when a workgroup posts epoch e, all have
@@ -660,7 +661,7 @@ __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const doub
       }
     }
     const unsigned long long *read = slots + (blockIdx.x % COARSE_PCG_COPIES) * copy + set;
-    const long long t0 = wall_clock64();
+    const unsigned t0 = (unsigned)wall_clock64();
     // the sums of block i < nb
     auto get = [&](int i, double (&x)[NV]) {
       if (G == 1) {
@@ -679,7 +680,7 @@ __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const doub
           x[k] = B::value(q[k]);
         }
         if (all) return;
-        if (wall_clock64() - t0 > a.wait) {
+        if ((int)((unsigned)wall_clock64() - t0) > (int)a.wait) {
           sh.lost = 1;
           return;
         }
@@ -738,10 +739,10 @@ __device__ __forceinline__ bool cp_sum(const CoarsePcg &a, int epoch, const doub
 // value that is still empty has not arrived).
 template <typename T>
 __device__ __forceinline__ void cp_fetch(const typename CpBits<T>::U *__restrict__ zx, const int32_t *ids, T *zh,
-                                         int nh, int *lost, long long wait, int first, int count) {
+                                         int nh, int *lost, int wait, int first, int count) {
   using B = CpBits<T>;
   constexpr int NF = sizeof(T) == 4 ? 2 : 1;  // nodes whose loads are in flight together
-  const long long t0 = wall_clock64();
+  const unsigned t0 = (unsigned)wall_clock64();
   for (int u = (int)threadIdx.x - first; u < nh; u += NF * count) {
     typename B::U q[NF][3];
     int64_t from[NF];
@@ -761,7 +762,7 @@ __device__ __forceinline__ void cp_fetch(const typename CpBits<T>::U *__restrict
 #pragma unroll
         for (int k = 0; k < 3; ++k) all = all && q[f][k] != B::EMPTY;
       if (all) break;
-      if (wall_clock64() - t0 > wait) {
+      if ((int)((unsigned)wall_clock64() - t0) > wait) {
         *lost = 1;
         break;
       }
@@ -831,9 +832,10 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
   __syncthreads();  // ids
   int epoch = 0, it = 0;
   double sum[2], pq[1];
-  bool ok = cp_sum<2, RPT, false, true>(a, epoch++, v, sum, sh, [z0, ids, zh, nh, lost = &sh.lost, wait = a.wait](int t, int c) {
-    cp_fetch<T>(z0, ids, zh, nh, lost, wait, t, c);
-  });
+  bool ok = cp_sum<2, RPT, false, true>(
+      a, epoch++, v, sum, sh, [z0, ids, zh, nh, lost = &sh.lost, wait = (int)a.wait](int t, int c) {
+        cp_fetch<T>(z0, ids, zh, nh, lost, wait, t, c);
+      });
   double rz = sum[0], beta = 0.0;
   const double rr0 = sum[1];
   while (ok && it < a.maxit) {
@@ -863,18 +865,16 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
       c[s][0] = (double)po[s] * (double)q[s];
     }
     ok = cp_sum<1, RPT, true, false>(a, epoch++, c, pq, sh, [](int, int) {});
-    if (!ok) break;
-    // a breakdown ends with a step of length zero, as k_pcg_update2 makes it: a direction
-    // that is not finite shows in x
-    const bool broke = !(pq[0] > 0.0);
-    const T al = broke ? T(0) : (T)(rz / pq[0]);
-#pragma unroll
-    for (int s = 0; s < RPT; ++s) x[s] += al * po[s];
-    if (broke) break;
+    if (!ok || !(pq[0] > 0.0)) {  // breakdown: x as it is; the host looks at p.q
+      if (g == 0 && tid == 0) a.sc[1] = pq[0];
+      break;
+    }
+    const T al = (T)(rz / pq[0]);
     U *const zw = it & 1 ? z0 : z1, *const zo = it & 1 ? z1 : z0;
 #pragma unroll
     for (int s = 0; s < RPT; ++s) {
       const int row = tid + s * CP_NT;
+      x[s] += al * po[s];
       r[s] = r[s] - al * q[s];
       z[s] = di[s] * r[s];
       if (row < rows) {
@@ -884,9 +884,10 @@ __global__ __launch_bounds__(CP_NT) void k_coarse_pcg(CoarsePcg a) {
       v[s][0] = (double)r[s] * (double)z[s];
       v[s][1] = (double)r[s] * (double)r[s];
     }
-    ok = cp_sum<2, RPT, false, false>(a, epoch++, v, sum, sh, [zw, ids, zh, nh, lost = &sh.lost, wait = a.wait](int t, int c) {
-      cp_fetch<T>(zw, ids, zh, nh, lost, wait, t, c);
-    });
+    ok = cp_sum<2, RPT, false, false>(
+        a, epoch++, v, sum, sh, [zw, ids, zh, nh, lost = &sh.lost, wait = (int)a.wait](int t, int c) {
+          cp_fetch<T>(zw, ids, zh, nh, lost, wait, t, c);
+        });
     if (!ok) break;
     ++it;
     beta = rz != 0.0 ? sum[0] / rz : 0.0;
