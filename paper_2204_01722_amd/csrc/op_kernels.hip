@@ -641,8 +641,8 @@ __global__ __launch_bounds__(QT<Q>::NT, MODE == 7 ? 4 : 1) void k_jacobian_lines
     const double *__restrict__ lam_e, T *__restrict__ ev, int64_t E, const double *__restrict__ stop,
     double *__restrict__ state_out, unsigned *__restrict__ flags, const double *__restrict__ u,
     double *__restrict__ mub, double *__restrict__ lamb) {
-  constexpr bool KEEP = MODE == 9, APPLY = MODE == 0 || KEEP, STATE = APPLY || MODE == 6, TWO = MODE == 5 || MODE == 7, VJP = MODE == 6 || MODE == 7;
-  constexpr bool RES = MODE == 4 || MODE == 8;
+  constexpr bool KEEP = MODE == 9, APPLY = MODE == 0 || KEEP, RES = MODE == 4 || MODE == 8;
+  constexpr bool VJP = MODE == 6 || MODE == 7, TWO = MODE == 5 || MODE == 7, STATE = APPLY || MODE == 6;
   constexpr int NH = MODE == 2 ? 16 : MODE == 3 ? 19 : 9;
   static_assert(!RES || std::is_same<T, double>::value, "the residual form is FP64");
   if (stop && *stop != 0.0) return;  // a stopped PCG (uniform over the grid)
