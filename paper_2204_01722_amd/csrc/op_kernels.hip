@@ -377,14 +377,14 @@ __device__ __forceinline__ int64_t xcd_tile() {
 // 256 MB last-level cache for the assembly that follows; larger ones stream out with
 // nontemporal stores.  Measured, us an apply, plain / nontemporal record stores:
 //                                     one operator repeated   four operators in turn
-//   Q2 on 43^3 elements (52 MB)              90 / 93                 87 / 89
-//   Q4 on 34^3 (118 MB)                     194 / 203               205 / 195
-//   Q2 on 60^3 (140 MB)                     212 / 225               236 / 232
-//   Q4 on 37^3 (152 MB)                     261 / 258               262 / 259
-//   Q4 on 40^3 (192 MB)                     329 / 318               330 / 317
-//   Q2 on 72^3 (242 MB)                     418 / 400               415 / 403
-// The line is drawn for one operator, as in a Krylov solve, where it lies near 145 MB; for
-// operators in turn it lies between 52 and 118 MB.  An earlier form of the kernels with
+//   Q2 on 43^3 elements (52 MB)              77 / 85                 86 / 88
+//   Q4 on 34^3 (118 MB)                     170 / 181               204 / 195
+//   Q2 on 60^3 (140 MB)                     196 / 216               234 / 230
+//   Q4 on 37^3 (152 MB)                     248 / 237               260 / 256
+//   Q4 on 40^3 (192 MB)                     320 / 301               326 / 316
+//   Q2 on 72^3 (242 MB)                     413 / 394               411 / 400
+// The line is drawn for one operator, as in a Krylov solve, where it lies between 140 and 152
+// MB; for operators in turn it lies between 52 and 118 MB.  An earlier form of the kernels with
 // per-node stores: Q4 34^3 217 us against 188, Q2 43^3 88.4 against 87.2, Q2 86^3 785 against
 // 724.  In FP32 the per-node stores were as fast or faster.
 template <typename T>
@@ -402,35 +402,45 @@ bool keep_records(int64_t E, int P) {
 // by its write-back: residual alone 308 us on 34^3 Q4 elements (614 MiB) against 234
 // streaming.  Measured, us, residual and a Jacobian action behind it, plain / streaming:
 //                                one operator repeated   three in turn
-//   Q4 on 20^3 (125 MiB)                94 / 101            104 / 99
-//   22^3 (166 MiB)                     120 / 127            132 / 125
-//   23^3 (190 MiB)                     139 / 142            154 / 143
-//   24^3 (216 MiB)                     161 / 158            174 / 164
-//   25^3 (244 MiB)                     180 / 176            195 / 187
-//   Q2 on 40^3 (222 MiB)               152 / 155            165 / 154
-//   41^3 (240 MiB)                     163 / 167            178 / 168
-//   43^3 (276 MiB)                     185 / 186            202 / 194
-// The line is drawn for one operator: there it lies near 200 MiB at Q4 and near 276 at Q2, and
-// 240 is in between; with operators in turn streaming wins at every size measured.
+//   Q4 on 20^3 (125 MiB)                91 / 97             102 / 97
+//   22^3 (166 MiB)                     114 / 121            130 / 122
+//   23^3 (190 MiB)                     134 / 138            151 / 140
+//   24^3 (216 MiB)                     154 / 154            171 / 162
+//   25^3 (244 MiB)                     173 / 172            191 / 184
+//   Q2 on 40^3 (222 MiB)               148 / 152            165 / 153
+//   41^3 (240 MiB)                     159 / 163            178 / 165
+//   42^3 (257 MiB)                     173 / 173            193 / 179
+//   43^3 (276 MiB)                     182 / 183            202 / 193
+// (the residual alone at 25^3 115 / 99, at Q2 43^3 123 / 106).  The line is drawn for one
+// operator: the two meet near 216 MiB at Q4 and 257 at Q2, and 240 is in between; with operators
+// in turn streaming wins at every size measured.
 inline bool stream_state(int64_t tiles, int Q) {
   return (double)tiles * NSTATE * field_stride(Q) * sizeof(double) > 240.0 * (1 << 20);
 }
 
-// Inside a V-cycle or an eigenvalue estimate (Finish sm or pq), a linearisation of 48 to 168
+// Inside a V-cycle or an eigenvalue estimate (Finish sm or pq), a linearisation of 60 to 130
 // MiB is loaded with plain loads: it stays in the 256 MiB last-level cache beside the records
 // and vectors, and the next action (a smoothing step, an iteration, the level below) reads it
-// there.  Measured, us a V-cycle Q4 -> Q2 -> Q1 with four coarse iterations, plain /
-// nontemporal loads: FP64 on 12^3 elements (28 MiB) 320 / 320, 14^3 (43 MiB) 384 / 378, 16^3 (64
-// MiB) 439 / 453, 20^3 (125 MiB) 632 / 654, 22^3 (166 MiB) 820 / 810, 24^3 (216 MiB) 1050 / 991;
-// FP32 on 14^3 (22 MiB) 292 / 295, 18^3 (46 MiB) 382 / 385, 20^3 (63 MiB) 439 / 454, 25^3 (122
-// MiB) 668 / 685, 28^3 (172 MiB) 924 / 902: below 48 MiB the two are equal within the runs'
-// spread, from 166 MiB on plain loads lose.  A single action keeps the nontemporal loads: with
-// the states of five operators in turn, 20^3 FP64 takes 42.1 us with them and 47.3 with plain
-// ones.
+// there.  Measured, us, Q4 -> Q2 -> Q1, plain / nontemporal loads, a V-cycle with four coarse
+// iterations and a setup:
+//                 state       V-cycle       setup
+//   FP64 15^3     53 MiB    408 / 403   1035 / 1025
+//        16^3     64        440 / 447   1114 / 1129
+//        18^3     91        512 / 526   1341 / 1369
+//        20^3    125        631 / 649   1646 / 1696
+//        21^3    145        737 / 732   1846 / 1867
+//        22^3    166        812 / 801   2110 / 2083
+//   FP32 18^3     46        382 / 375    986 / 984
+//        20^3     63        437 / 443   1146 / 1159
+//        22^3     83        507 / 518   1359 / 1378
+//        25^3    122        673 / 666   1774 / 1813
+//        26^3    137        737 / 727   1968 / 1966
+// A single action keeps the nontemporal loads: with the states of five operators in turn, 20^3
+// FP64 takes 42.1 us with them and 47.3 with plain ones.
 template <typename T>
 bool keep_state(int64_t tiles, int Q) {
   const double b = (double)tiles * NSTATE * field_stride(Q) * sizeof(T);
-  return b >= 48.0 * (1 << 20) && b <= 168.0 * (1 << 20);
+  return b >= 60.0 * (1 << 20) && b <= 130.0 * (1 << 20);
 }
 
 __device__ __forceinline__ double mat_mu(double mu0, const double *mu_e, int64_t e) {

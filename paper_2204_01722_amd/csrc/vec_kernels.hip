@@ -522,9 +522,9 @@ __global__ __launch_bounds__(BS) void k_ell_pcg_nodes(int64_t nn, int W, const i
 // the memory side (about 1.5 us), the neighbours' z fetched while the first is under way,
 // and 81 LDS reads a row.  Measured per iteration, launch to launch: 11^3 nodes 24 -> 4.4 us
 // (FP64), 21^3 23.6 -> 5.8 us (FP64), 26^3 25 -> 6.8 us (FP32); a whole V-cycle Q4 -> Q2 -> Q1 to
-// a coarse tolerance of 1e-3, by launches against one launch: 20^3 elements FP64 998 -> 666 us
-// with a right-hand side of 17 coarse iterations, 2857 -> 1140 with one of 97; FP32 776 -> 470 and
-// 2429 -> 889; 25^3 FP32 1085 -> 709 (19) and 3164 -> 1206 (110).
+// a coarse tolerance of 1e-3, by launches against one launch: 20^3 elements FP64 1042 -> 674 us
+// with a right-hand side of 17 coarse iterations, 2852 -> 1114 with one of 97; FP32 806 -> 471 and
+// 2426 -> 889; 25^3 FP32 1117 -> 710 (19) and 3151 -> 1199 (110).
 // 512 rows a workgroup and not fewer, since the sums cost more with every workgroup that
 // posts and reads them (21^3 nodes: 55 workgroups 191 us a solve, 127 221, 251 275).  The sums
 // are taken over blocks of 256 rows, in the order of the launches' kernels, so that row-major
