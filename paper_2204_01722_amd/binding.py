@@ -177,12 +177,9 @@ _MODES = {STORED: STORED, "stored": STORED, RECOMPUTE: RECOMPUTE, "recompute": R
           "initial_tuned": INITIAL_TUNED, CURRENT_20: CURRENT_20, "current_20": CURRENT_20}
 
 
-def _named(table, v, what):
-    try:
-        return table[v]
-    except (KeyError, TypeError):
-        pass
-    # a value that equals a name without hashing like it: an array or tensor of one entry
+def _equal_to(table, v, what):
+    """The code of a name that ``v`` equals without hashing like it: an array or tensor of one
+    entry."""
     for name, code in table.items():
         if v == name:
             return code
@@ -190,11 +187,17 @@ def _named(table, v, what):
 
 
 def _prec(p):
-    return _named(_PRECS, p, "precision")
+    try:
+        return _PRECS[p]
+    except (KeyError, TypeError):
+        return _equal_to(_PRECS, p, "precision")
 
 
 def _mode(m):
-    return _named(_MODES, m, "mode")
+    try:
+        return _MODES[m]
+    except (KeyError, TypeError):
+        return _equal_to(_MODES, m, "mode")
 
 
 def _dtype(prec):
